@@ -270,7 +270,7 @@ __global__ void __launch_bounds__(256) k_kmc_ions(KmcParams P, StepConst K, Coun
 
 // Independent cells (unit parity): the three-reaction code when both recombination
 // rates of the cell are zero, the five-reaction code otherwise.
-__global__ void k_kmc_cells(KmcParams P, Key key, uint64_t n, const uint32_t* ids, int64_t* Xa,
+__global__ void __launch_bounds__(256, 2) k_kmc_cells(KmcParams P, Key key, uint64_t n, const uint32_t* ids, int64_t* Xa,
                             const double* ka, double dt, uint32_t step, int64_t* fa) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (uint64_t)gridDim.x * blockDim.x) {
@@ -304,9 +304,37 @@ int blocks_for(uint64_t n, int per_block, int max_blocks) {
 
 // Zero-dimensional reactors: nsteps steps per reactor in one launch, each reactor with
 // its own key (seed, realization) and stream cell id; X stays in registers.
-__global__ void k_kmc_run(KmcParams P, uint32_t seed, uint32_t real0, uint64_t n, const uint32_t* ids,
-                          const uint32_t* real, const uint32_t* nst, int64_t* Xa, const double* ka,
-                          double dt, uint32_t step0, uint32_t nsteps0, int64_t* fa) {
+//
+// The steps of one reactor are a serial chain, but the first word of a step's stream
+// depends only on the step, and most steps of the hybrid method are one SSA excursion
+// whose first waiting time already ends beyond the step (ssa_reach): nothing changes.  A
+// thread therefore draws the first words of kRunBatch steps together (independent Philox
+// chains in flight), skips the quiet ones by comparing their exponents with the
+// threshold of the present state, and runs the method only for the others, one at a time.
+// Bound by the Philox rounds (about 110 VALU instructions per step and wavefront): 10^6
+// reactors x 50 steps at 10 MV/m 1.96 -> 0.29 ms, 4096 x 275 steps 0.69 -> 0.106 ms (one
+// step at a time, with a double logarithm and two divisions each, before; the compiler's
+// 128-register default for unbounded launches also spilled 884 bytes a lane).
+constexpr int kRunBatch = 8;
+
+// Threshold of a quiet step from state X: the first exponent beyond it leaves the state as
+// it is.  -inf if nothing can fire, +inf if the step is not one SSA excursion.
+__device__ __forceinline__ float quiet_reach(const KmcParams& P, const State& X, const double k[3], double dt) {
+  const double a1 = k[0] * (double)X.e, a2 = k[1] * (double)X.e, a3 = k[2] * (double)X.e;
+  const double A = a1 + a2 + a3;
+  if (!(A > 0.0)) return -INFINITY;
+  if (P.mode != ITOKMC_KMC_HYBRID) return INFINITY;
+  const bool crit2 = (a2 > 0.0) && X.e < (int64_t)P.nc;
+  const double h = fmin(dt, leap_bound(P, X, a1, a2, a3, crit2));
+  if (h != dt || !(A * h <= 1.0)) return INFINITY;
+  return ssa_reach(A, h);
+}
+
+// One wavefront per workgroup: a few thousand reactors then spread over every CU.
+__global__ void __launch_bounds__(64, 2) k_kmc_run(KmcParams P, uint32_t seed, uint32_t real0, uint64_t n,
+                                                    const uint32_t* ids, const uint32_t* real,
+                                                    const uint32_t* nst, int64_t* Xa, const double* ka,
+                                                    double dt, uint32_t step0, uint32_t nsteps0, int64_t* fa) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (uint64_t)gridDim.x * blockDim.x) {
     const Key key{seed, real ? real[i] : real0};
@@ -317,12 +345,37 @@ __global__ void k_kmc_run(KmcParams P, uint32_t seed, uint32_t real0, uint64_t n
     if (ka[5 * i + 3] == 0.0 && ka[5 * i + 4] == 0.0) {
       State X{Xa[4 * i], Xa[4 * i + 1], Xa[4 * i + 2], Xa[4 * i + 3]};
       const double k[3] = {ka[5 * i], ka[5 * i + 1], ka[5 * i + 2]};
-      for (uint32_t s = 0; s < nsteps; ++s) {
-        CellStream st;
-        st.init(id, step0 + s, TAG_KMC, 0, key);
-        int64_t f[3];
-        advance(P, X, k, dt, st, f);
-        F[0] += f[0]; F[1] += f[1]; F[2] += f[2];
+      float reach = quiet_reach(P, X, k, dt);
+      for (uint32_t s0 = 0; s0 < nsteps;) {
+        float ex[kRunBatch];
+#pragma unroll
+        for (int q = 0; q < kRunBatch; ++q)
+          ex[q] = ssa_exponent(philox_block(id, 0, step0 + s0 + (uint32_t)q, TAG_KMC, 0, key).x);
+        const uint32_t left = nsteps - s0;
+        const uint32_t in = left < (uint32_t)kRunBatch ? (1u << left) - 1u : (1u << kRunBatch) - 1u;
+        uint32_t todo = in;  // steps of the batch not yet passed
+        for (;;) {
+          uint32_t loud = 0;
+#pragma unroll
+          for (int q = 0; q < kRunBatch; ++q) loud |= ex[q] > reach ? 0u : (1u << q);
+          loud &= todo;
+          if (loud == 0u) break;
+          const uint32_t q = (uint32_t)__ffs((int)loud) - 1u;
+          todo &= ~((2u << q) - 1u);
+          CellStream st;
+          st.init(id, step0 + s0 + q, TAG_KMC, 0, key);
+          int64_t f[3];
+          State Y = X;
+          if (advance_fast(P, Y, k, dt, st, f)) {
+            X = Y;
+          } else {
+            st.init(id, step0 + s0 + q, TAG_KMC, 0, key);
+            advance(P, X, k, dt, st, f);
+          }
+          F[0] += f[0]; F[1] += f[1]; F[2] += f[2];
+          reach = quiet_reach(P, X, k, dt);
+        }
+        s0 += left < (uint32_t)kRunBatch ? left : (uint32_t)kRunBatch;
       }
       Xa[4 * i] = X.e; Xa[4 * i + 1] = X.p; Xa[4 * i + 2] = X.m; Xa[4 * i + 3] = X.g;
     } else {
@@ -414,7 +467,7 @@ hipError_t launch_stop_end(itokmc_ctx* ctx) {
 hipError_t launch_kmc_run(itokmc_ctx* ctx, uint64_t n, const uint32_t* ids, const uint32_t* real,
                           const uint32_t* nst, int64_t* X, const double* k, double dt, uint32_t step0,
                           uint32_t nsteps, int64_t* fires) {
-  k_kmc_run<<<blocks_for(n, 256, 8192), 256, 0, ctx->s>>>(params(ctx), ctx->d.seed, ctx->d.realization,
+  k_kmc_run<<<blocks_for(n, 64, 32768), 64, 0, ctx->s>>>(params(ctx), ctx->d.seed, ctx->d.realization,
                                                          n, ids, real, nst, X, k, dt, step0, nsteps,
                                                          fires);
   return hipGetLastError();

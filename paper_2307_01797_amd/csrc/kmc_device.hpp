@@ -35,6 +35,22 @@ __device__ inline double leap_bound(const KmcParams& P, const State& X, double a
   return best;
 }
 
+// Word x of an SSA waiting time, seen from `left` before the end of the excursion: true if
+// the time log(1 / u) / A certainly ends beyond it, by the hardware logarithm.  The
+// single-precision exponent is within 1e-5 of the double one (u is rounded once, v_log_f32
+// to an ulp of a value of at most 32) and the threshold carries 1e-4 and a hundredth of a
+// percent, so a true answer is the answer of the double comparison, whose own roundings
+// are 1e-13 at most; a false one decides nothing.  Most draws end beyond the step (A dt is
+// well below one), and those need no double logarithm and no divisions.  Infinite or NaN
+// thresholds give false.
+__device__ __forceinline__ float ssa_exponent(uint32_t x) {
+  return -0.69314718f * __builtin_amdgcn_logf(u_ocf(x));
+}
+__device__ __forceinline__ float ssa_reach(double A, double left) {
+  const float r = (float)(A * left);
+  return r + (1e-4f + 1e-4f * r);
+}
+
 // Whole-network SSA for at most nssa events inside h; returns the time advanced.
 __device__ inline double ssa_run(const KmcParams& P, State& X, const double k[3], double h,
                           CellStream& st, int64_t f[3]) {
@@ -44,7 +60,9 @@ __device__ inline double ssa_run(const KmcParams& P, State& X, const double k[3]
     const double a1 = k[0] * (double)X.e, a2 = k[1] * (double)X.e, a3 = k[2] * (double)X.e;
     const double A = a1 + a2 + a3;
     if (!(A > 0.0)) return h;
-    const double delta = log(1.0 / u_oc(st.next())) / A;
+    const uint32_t x = st.next();
+    if (ssa_exponent(x) > ssa_reach(A, h - tp)) return h;
+    const double delta = log(1.0 / u_oc(x)) / A;
     if (tp + delta > h) return h;
     const double target = u_co(st.next()) * A;
     // the first reaction whose cumulative propensity exceeds u A; if rounding leaves
@@ -256,7 +274,9 @@ __device__ inline double ssa_run5(const KmcParams& P, State5& X, const double k[
     props5(X, k, a);
     const double A = a[0] + a[1] + a[2] + a[3] + a[4];
     if (!(A > 0.0)) return h;
-    const double delta = log(1.0 / u_oc(st.next())) / A;
+    const uint32_t x = st.next();
+    if (ssa_exponent(x) > ssa_reach(A, h - tp)) return h;
+    const double delta = log(1.0 / u_oc(x)) / A;
     if (tp + delta > h) return h;
     const int j = select5(a, all, A, u_co(st.next()));
     fire5(X, j, 1);
