@@ -9,7 +9,10 @@
 // it does the removal and the products of cells with at most kLightMax particles and
 // products, checks whether they need merging or splitting, and queues the cells that
 // do (merge only) and the larger cells (everything) for the wavefront-per-cell pass.
-// The arithmetic and its order are the same on both paths.
+// The number of particles counts only where the pass has to look at them (removal, merge
+// trigger): products alone touch no particle of the cell, so without merging a gaining
+// cell of any size stays in the light pass (5e7 particles in 7e6 cells: wavefront pass
+// 0.51 -> 0.11 ms).  The arithmetic and its order are the same on both paths.
 #include <math.h>
 
 #include <type_traits>
@@ -48,7 +51,7 @@ __global__ void __launch_bounds__(256) k_couple_light(Bank b, Counters* ctr, Ste
       const uint32_t s = start[c], e = j + 1 < n_occ ? start[occ[j + 1]] : sorted;
       const int32_t d = dN[j];
       const uint32_t M = d > 0 ? ((uint32_t)d < (uint32_t)n_new ? (uint32_t)d : (uint32_t)n_new) : 0u;
-      if (e - s > kLightMax || M > kLightMax) {
+      if (M > kLightMax || (e - s > kLightMax && (d < 0 || n_ppc > 0))) {
         to_full = true;
       } else {
         if (d < 0) removed += remove_weight_lane(b, s, e, (uint32_t)(-d));
