@@ -498,14 +498,28 @@ __global__ void __launch_bounds__(kBlock) k_scan_down(const unsigned long long* 
   }
 }
 
+// Move every live particle to start[cell] + rank.  Two forms:
+//
+// * scatter: each source stores its six words at the destination.  Destinations of
+//   neighbouring sources interleave, so lines are partly written from several XCDs' L2s,
+//   and each such line costs memory a read and more than one write.
+// * place and gather (from != null and more than kGatherMin particles): a source stores
+//   its own slot at its destination (one word, in the destination bank's unused rank
+//   array), and k_gather reads the particles from there: neighbouring particles' loads
+//   share lines, and the stores are whole lines.
+//
+// At 5.2e7 particles (7e6 cells) the scatter took 1.73 ms, the two passes take 0.28 + 1.05
+// (2.4 TB/s of the 60 bytes), and 11.9 against 1.8 + 6.6 ms on an unsorted seed; at 4.5e7
+// near the particle cap 2.40 against 0.44 + 1.32 ms; at 8e6 particles 0.147 against 0.045 +
+// 0.110 ms, so the line is drawn between them.  The count is known on the device only.
+constexpr uint32_t kGatherMin = 1u << 24;
+
 template <typename T>
 __global__ void __launch_bounds__(kBlock) k_scatter(Bank a, Bank b, Counters* ctr, int which,
-                                                   const uint32_t* start, uint32_t cap) {
+                                                   const uint32_t* start, uint32_t cap, uint32_t* from) {
   if (ctr->halt) return;
   const uint32_t n = min(ctr->n[which], cap);
-  if (n <= 2u * gridDim.x * blockDim.x) {
-    // at most two passes of the grid: one particle per thread and pass (0.22 ms at
-    // 9.5e6 particles, against 0.24 ms in the paired form below)
+  if (from == nullptr || n <= kGatherMin) {
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
       const uint32_t w = a.w[i];
       if (w == 0) continue;
@@ -515,10 +529,8 @@ __global__ void __launch_bounds__(kBlock) k_scatter(Bank a, Bank b, Counters* ct
     }
     return;
   }
-  // many passes: two particles per thread and pass, every load unconditional so that
-  // both particles' loads are in flight together (2.60 against 3.06 ms at 6.9e7
-  // particles); a dead slot (weight 0) or a second index past n reads slot 0 and cell 0
-  // instead (one cached line for all such lanes) and stores nothing
+  // two particles per thread and pass, all loads in flight together; a dead slot (weight
+  // 0) or a second index past n reads slot 0 and cell 0 instead and stores nothing
   const uint32_t stride = gridDim.x * blockDim.x * 2u;
   for (uint32_t i0 = blockIdx.x * blockDim.x * 2u + threadIdx.x; i0 < n; i0 += stride) {
     const uint32_t i1 = i0 + blockDim.x;
@@ -526,12 +538,44 @@ __global__ void __launch_bounds__(kBlock) k_scatter(Bank a, Bank b, Counters* ct
     const uint32_t j0 = w0 ? i0 : 0u, j1 = w1 ? i1 : 0u;
     const uint32_t c0 = a.cell[j0], c1 = a.cell[j1];
     const uint32_t r0 = a.rank[j0], r1 = a.rank[j1];
-    const T x0 = as<T>(a.ox)[j0], y0 = as<T>(a.oy)[j0], z0 = as<T>(a.oz)[j0];
-    const T x1 = as<T>(a.ox)[j1], y1 = as<T>(a.oy)[j1], z1 = as<T>(a.oz)[j1];
-    const uint64_t d0 = a.id[j0], d1 = a.id[j1];
     const uint32_t s0 = start[w0 ? c0 : 0u], s1 = start[w1 ? c1 : 0u];
-    if (w0) put<T>(b, s0 + r0, c0, x0, y0, z0, w0, d0);
-    if (w1) put<T>(b, s1 + r1, c1, x1, y1, z1, w1, d1);
+    if (w0) from[s0 + r0] = i0;
+    if (w1) from[s1 + r1] = i1;
+  }
+}
+
+// Second pass of the place-and-gather form (returns at once after a scatter).  Each XCD
+// reads one contiguous eighth of the destinations, so that the source lines its
+// workgroups share stay in its L2 (5%), and the stores bypass the caches (3%): nothing
+// reads them before the next kernel.
+template <typename T>
+__device__ __forceinline__ void put_nt(const Bank& b, uint32_t q, uint32_t cell, T ox, T oy, T oz,
+                                       uint32_t w, uint64_t id) {
+  __builtin_nontemporal_store(cell, &b.cell[q]);
+  __builtin_nontemporal_store(ox, &as<T>(b.ox)[q]);
+  __builtin_nontemporal_store(oy, &as<T>(b.oy)[q]);
+  __builtin_nontemporal_store(oz, &as<T>(b.oz)[q]);
+  __builtin_nontemporal_store(w, &b.w[q]);
+  __builtin_nontemporal_store(id, &b.id[q]);
+}
+template <typename T>
+__global__ void __launch_bounds__(kBlock) k_gather(Bank a, Bank b, Counters* ctr, int which, uint32_t cap,
+                                                  const uint32_t* from) {
+  if (ctr->halt || min(ctr->n[which], cap) <= kGatherMin) return;
+  const uint32_t n = ctr->sorted;
+  constexpr uint32_t kChunk = 2u * kBlock;  // the grid is a multiple of 8 workgroups
+  const uint32_t chunks = (n + kChunk - 1u) / kChunk, per = (chunks + 7u) / 8u;
+  const uint32_t xcd = blockIdx.x & 7u, last = min(chunks, (xcd + 1u) * per);
+  for (uint32_t c = xcd * per + (blockIdx.x >> 3); c < last; c += gridDim.x >> 3) {
+    const uint32_t q0 = c * kChunk + threadIdx.x, q1 = q0 + kBlock;
+    if (q0 >= n) continue;
+    const uint32_t i0 = from[q0], i1 = from[q1 < n ? q1 : q0];
+    const uint32_t c0 = a.cell[i0], c1 = a.cell[i1], w0 = a.w[i0], w1 = a.w[i1];
+    const T x0 = as<T>(a.ox)[i0], y0 = as<T>(a.oy)[i0], z0 = as<T>(a.oz)[i0];
+    const T x1 = as<T>(a.ox)[i1], y1 = as<T>(a.oy)[i1], z1 = as<T>(a.oz)[i1];
+    const uint64_t d0 = a.id[i0], d1 = a.id[i1];
+    put_nt<T>(b, q0, c0, x0, y0, z0, w0, d0);
+    if (q1 < n) put_nt<T>(b, q1, c1, x1, y1, z1, w1, d1);
   }
 }
 
@@ -723,9 +767,9 @@ hipError_t launch_scan(itokmc_ctx* ctx) {
 hipError_t launch_scatter_raw(Bank a, Bank b, Counters* ctr, int which, const uint32_t* start,
                               uint32_t cap, int fp64, int grid, hipStream_t s) {
   if (fp64)
-    k_scatter<double><<<grid, kBlock, 0, s>>>(a, b, ctr, which, start, cap);
+    k_scatter<double><<<grid, kBlock, 0, s>>>(a, b, ctr, which, start, cap, nullptr);
   else
-    k_scatter<float><<<grid, kBlock, 0, s>>>(a, b, ctr, which, start, cap);
+    k_scatter<float><<<grid, kBlock, 0, s>>>(a, b, ctr, which, start, cap, nullptr);
   return hipGetLastError();
 }
 
@@ -734,12 +778,17 @@ hipError_t launch_scatter(itokmc_ctx* ctx) {
   // particles with up to 32768 against 0.224 ms with 4096 (and 0.21 ms with 16384 or
   // 65536)
   const int g = grid_for(ctx->cap, kBlock, 32768);
+  Bank &a = ctx->bank[ctx->cur], &b = ctx->bank[1 - ctx->cur];
+  const uint32_t cap = (uint32_t)ctx->cap;
+  uint32_t* from = cap > kGatherMin ? b.rank : nullptr;
   if (fp64(ctx))
-    k_scatter<double><<<g, kBlock, 0, ctx->s>>>(ctx->bank[ctx->cur], ctx->bank[1 - ctx->cur],
-                                                 ctx->ctr, ctx->cur, ctx->start, (uint32_t)ctx->cap);
+    k_scatter<double><<<g, kBlock, 0, ctx->s>>>(a, b, ctx->ctr, ctx->cur, ctx->start, cap, from);
   else
-    k_scatter<float><<<g, kBlock, 0, ctx->s>>>(ctx->bank[ctx->cur], ctx->bank[1 - ctx->cur],
-                                                ctx->ctr, ctx->cur, ctx->start, (uint32_t)ctx->cap);
+    k_scatter<float><<<g, kBlock, 0, ctx->s>>>(a, b, ctx->ctr, ctx->cur, ctx->start, cap, from);
+  if (from) {
+    if (fp64(ctx)) k_gather<double><<<g, kBlock, 0, ctx->s>>>(a, b, ctx->ctr, ctx->cur, cap, from);
+    else k_gather<float><<<g, kBlock, 0, ctx->s>>>(a, b, ctx->ctr, ctx->cur, cap, from);
+  }
   return hipGetLastError();
 }
 
