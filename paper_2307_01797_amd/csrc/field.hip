@@ -43,6 +43,7 @@ struct Level {
   void* u;    // correction
   void* f;    // right-hand side (scaled by h^2)
   void* eps;  // cell coefficient 1 + sigma dt / eps0
+  void* cf;   // small levels: face coefficients and diagonal (k_small_setup)
 };
 
 struct Coef {
@@ -827,18 +828,25 @@ __global__ void __launch_bounds__(256) k_field_prep(StepConst K, const uint32_t*
   if (threadIdx.x == 0) partial[blockIdx.x] = acc;
 }
 
+// Mean of the eight children's coefficients of coarse cell (i, j, k).
+template <typename T>
+__device__ __forceinline__ T eps_child_mean(const T* ef, int fnx, int fny, int fsplit, int i, int j, int k) {
+  double s = 0.0;
+#pragma unroll
+  for (int d = 0; d < 8; ++d) {
+    const int fi = 2 * i + (d & 1), fj = 2 * j + ((d >> 1) & 1), fk = 2 * k + (d >> 2);
+    s += (double)ef[fsplit ? pos_of<true>(fi, fj, fk, fnx, fny) : pos_of<false>(fi, fj, fk, fnx, fny)];
+  }
+  return (T)(s * 0.125);
+}
+
 template <typename T>
 __global__ void k_eps_restrict(const T* ef, int fnx, int fny, int fsplit, T* ec, int cnx, int cny, int cnz,
                                int csplit) {
   const uint32_t n = (uint32_t)cnx * cny * cnz;
   for (uint32_t c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) {
     const int i = c % cnx, j = (c / cnx) % cny, k = c / (cnx * cny);
-    double s = 0.0;
-    for (int d = 0; d < 8; ++d) {
-      const int fi = 2 * i + (d & 1), fj = 2 * j + ((d >> 1) & 1), fk = 2 * k + (d >> 2);
-      s += (double)ef[fsplit ? pos_of<true>(fi, fj, fk, fnx, fny) : pos_of<false>(fi, fj, fk, fnx, fny)];
-    }
-    ec[csplit ? pos_of<true>(i, j, k, cnx, cny) : (size_t)c] = (T)(s * 0.125);
+    ec[csplit ? pos_of<true>(i, j, k, cnx, cny) : (size_t)c] = eps_child_mean<T>(ef, fnx, fny, fsplit, i, j, k);
   }
 }
 
@@ -1127,194 +1135,166 @@ __global__ void __launch_bounds__(128) k_prolong3(T* u, int nx, int ny, int nz, 
   u[(size_t)p + (size_t)nx * ((size_t)j + (size_t)ny * k)] += prolong_value<T>(uc, cnx, cny, cnz, i, j, k);
 }
 
-// `sweeps` red-black sweeps of a small level inside one workgroup (a barrier between
-// colours), the cell updates of the one-colour launches.
-template <typename T>
-__device__ __forceinline__ void rb_sweeps(T* u, const T* f, const T* eps, int nx, int ny, int nz,
-                                          int sweeps) {
-  const int n = nx * ny * nz;
-  for (int s = 0; s < sweeps; ++s)
-    for (int color = 0; color < 2; ++color) {
-      for (int c = threadIdx.x; c < n; c += blockDim.x) {
-        const int i = c % nx, j = (c / nx) % ny, k = c / (nx * ny);
-        if (((i + j + k) & 1) != color) continue;
-        smooth_cell<T>(u, f, eps, nx, ny, nz, i, j, k);
-      }
-      __syncthreads();
-    }
-}
-
-// Levels of at most kSmallLevel cells: all pre- or post-sweeps in one launch.
+// ---- small levels ---------------------------------------------------------------------
+// Levels of at most kSmallLevel cells below the finest (and a single-level grid) run their
+// sweeps in one workgroup with the correction in LDS.  Their face coefficients and
+// diagonals do not change within a solve, so one launch per solve forms them for all of
+// them (k_small_setup: three face coefficients towards the + neighbours and the diagonal
+// per cell; the harmonic mean is symmetric in its two cells, so both read the same
+// value).  In the sweeps a thread owns up to NR cells of each colour and keeps their
+// coefficients, diagonals and right-hand sides in registers: a colour is six LDS reads
+// and the update.  Owning cells by colour keeps every lane of a wavefront at work in each
+// colour.  The arithmetic and its order are op_row's and smooth_div's (a face outside the
+// domain has coefficient zero and the cell itself as its neighbour, which adds zero).
+// Bound by the latency of a colour (LDS, a chain of six additions, the division, a
+// barrier).  16^3 in double: 33.8 -> 11.4 us per launch; 9x7x11 bottom, 60 sweeps in double:
+// 180 -> 29 us; 11x9x13 bottom, 68 sweeps in single: 44 -> 28.5 us.
 constexpr uint32_t kSmallLevel = 4096;
-// LDS that one small-level launch may stage: correction, right-hand side and
-// coefficient of the level (3 n values).
-constexpr size_t kSmallLds = 65536;
+static_assert(kBottomMaxCells <= (int)kSmallLevel, "the coarsest level runs as a small level");
+
+struct SmallLevels {
+  int count;
+  int nx[kMaxLevels], ny[kMaxLevels], nz[kMaxLevels];
+  void* eps[kMaxLevels];
+  void* cf[kMaxLevels];  // x, y and z face coefficients and the diagonal, n values each
+};
+
+// Coefficients of the small levels, finest first, in one workgroup: the cell coefficient
+// of each (restricted from the level above it; the first one from ef unless that is null:
+// a single-level grid) and its faces.
 template <typename T>
-inline bool small_fits_lds(uint32_t n) { return 3 * (size_t)n * sizeof(T) <= kSmallLds; }
-
-template <typename T>
-__global__ void __launch_bounds__(1024) k_sweeps_small(T* u, const T* f, const T* eps, int nx, int ny,
-                                                      int nz, int sweeps) {
-  rb_sweeps<T>(u, f, eps, nx, ny, nz, sweeps);
-}
-
-// Launch shapes of the LDS form, threads x cells per thread: levels of up to 64 cells
-// run in one wavefront (its barriers cost little), larger ones in 1024 threads x 4
-// cells (single precision) or 512 x 8 (double precision, which keeps the registers of
-// a thread's cells within its waves' budget).
-template <typename T> constexpr int kSmallThreads = sizeof(T) == 8 ? 512 : 1024;
-template <typename T> constexpr int kSmallCells = (int)kSmallLevel / kSmallThreads<T>;
-
-// Red-black sweeps of a small level held in LDS, single precision: each of the NT
-// threads owns the cells t + r NT (r < NC) and keeps their face coefficients, diagonal
-// and right-hand side in registers, so that a sweep reads only the six neighbour
-// values.  The coefficients and the update are those of op_row and smooth_cell, in the
-// same order (same values).
-template <typename T, int NT, int NC>
-__device__ __forceinline__ void small_sweeps_cached(T* su, const T* sf, const T* se, int nx, int ny, int nz,
-                                                    int sweeps) {
-  const int n = nx * ny * nz, sy = nx, sz = nx * ny;
-  T bq[NC][6], dg[NC], fr[NC];
-  int cr[NC];
-  uint32_t meta[NC];  // bits 0-5: face q inside; bit 6: colour; bit 7: owned cell
-#pragma unroll
-  for (int r = 0; r < NC; ++r) {
-    const int c = (int)threadIdx.x + r * NT;
-    cr[r] = c < n ? c : 0;
-    meta[r] = 0;
-    dg[r] = (T)1;
-    fr[r] = (T)0;
-    if (c < n) {
-      const int i = c % nx, j = (c / nx) % ny, k = c / sz;
+__global__ void __launch_bounds__(1024) k_small_setup(SmallLevels L, const T* ef, int fnx, int fny, int fsplit) {
+  for (int l = 0; l < L.count; ++l) {
+    const int nx = L.nx[l], ny = L.ny[l], nz = L.nz[l], n = nx * ny * nz, sy = nx, sz = nx * ny;
+    T* const e = reinterpret_cast<T*>(L.eps[l]);
+    T* const cf = reinterpret_cast<T*>(L.cf[l]);
+    if (ef)
+      for (int c = threadIdx.x; c < n; c += 1024)
+        e[c] = eps_child_mean<T>(ef, fnx, fny, fsplit, c % nx, (c / nx) % ny, c / sz);
+    __syncthreads();
+    for (int c = threadIdx.x; c < n; c += 1024) {
       bool in[6];
-      faces_in(i, j, k, nx, ny, nz, in);
+      faces_in(c % nx, (c / nx) % ny, c / sz, nx, ny, nz, in);
       const int off[6] = {in[0] ? -1 : 0, in[1] ? 1 : 0, in[2] ? -sy : 0,
                           in[3] ? sy : 0, in[4] ? -sz : 0, in[5] ? sz : 0};
-      const T ec = se[c];
+      const T ec = e[c];
       T d = 0;
-      uint32_t m = 0x80u | ((uint32_t)((i + j + k) & 1) << 6);
 #pragma unroll
       for (int q = 0; q < 6; ++q) {
-        const T b = hmean_s(ec, se[c + off[q]]);
-        bq[r][q] = b;
+        const T b = hmean_s(ec, e[c + off[q]]);
         d = in[q] ? d + b : (q >= 4 ? d + (T)2 * ec : d);
-        m |= in[q] ? (1u << q) : 0u;
+        if (q & 1) cf[(size_t)(q >> 1) * n + c] = in[q] ? b : (T)0;
       }
-      dg[r] = d;
-      fr[r] = sf[c];
-      meta[r] = m;
+      cf[(size_t)3 * n + c] = d;
     }
+    ef = e;
+    fnx = nx;
+    fny = ny;
+    fsplit = 0;
   }
-  for (int it = 0; it < sweeps; ++it)
-    for (int color = 0; color < 2; ++color) {
-      const uint32_t want = 0x80u | ((uint32_t)color << 6);
+}
+
+// One small level (see above): pre-smoothing with the restriction of the residual
+// (fc_out), prolongation of the coarse correction (uc_in) with post-smoothing, or the
+// coarsest level's sweeps.  LDS: the correction, and with fc_out the residual.
+template <typename T, int NR, int MAXT>
+__global__ void __launch_bounds__(MAXT) k_small_level(T* u, const T* f, const T* cf, int nx, int ny, int nz,
+                                                      int sweeps, bool zero_u, const T* uc_in, T* fc_out,
+                                                      T* uc_out, int cnx, int cny, int cnz) {
+  extern __shared__ __align__(16) char smem[];
+  const int n = nx * ny * nz, sy = nx, sz = nx * ny, h = (nx + 1) >> 1, NT = (int)blockDim.x;
+  T* const su = reinterpret_cast<T*>(smem);
+  T* const sr = su + n;
+  T b[2][NR][6], dg[2][NR], fr[2][NR];
+  int nb[2][NR][6], cell[2][NR];  // cell: -1 past the colour's cells
 #pragma unroll
-      for (int r = 0; r < NC; ++r) {
-        if ((meta[r] & 0xC0u) != want) continue;
-        const int c = cr[r];
-        const uint32_t m = meta[r];
-        const int off[6] = {(m & 1u) ? -1 : 0, (m & 2u) ? 1 : 0, (m & 4u) ? -sy : 0,
-                            (m & 8u) ? sy : 0, (m & 16u) ? -sz : 0, (m & 32u) ? sz : 0};
-        T un[6];
+  for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int q = 0; q < 6; ++q) un[q] = su[c + off[q]];
-        T acc = 0;
+    for (int r = 0; r < NR; ++r) {
+      // the colour's cells row by row: position m of a row's colour q is x = 2 m + parity
+      const int p = (int)threadIdx.x + r * NT, row = p / h, m = p - row * h;
+      const int k = row / ny, j = row - k * ny, i = 2 * m + ((j + k + q) & 1);
+      const bool own = k < nz && i < nx;
+      const int c = own ? i + sy * j + sz * k : 0;
+      cell[q][r] = own ? c : -1;
+      bool in[6];
+      faces_in(own ? i : 0, own ? j : 0, own ? k : 0, nx, ny, nz, in);
+      const int off[6] = {in[0] ? -1 : 0, in[1] ? 1 : 0, in[2] ? -sy : 0,
+                          in[3] ? sy : 0, in[4] ? -sz : 0, in[5] ? sz : 0};
 #pragma unroll
-        for (int q = 0; q < 6; ++q) acc = ((m >> q) & 1u) ? acc + bq[r][q] * un[q] : acc;
-        su[c] = smooth_div(fr[r] + acc, dg[r]);
+      for (int a = 0; a < 6; ++a) {
+        nb[q][r][a] = c + off[a];
+        // the face below a cell is the + face of its lower neighbour
+        const T v = cf[(size_t)(a >> 1) * n + ((a & 1) ? c : c + off[a])];
+        b[q][r][a] = in[a] ? v : (T)0;
+      }
+      dg[q][r] = cf[(size_t)3 * n + c];
+      fr[q][r] = f[c];
+      T v = zero_u ? (T)0 : u[c];
+      if (uc_in && own) v = v + prolong_value<T>(uc_in, cnx, cny, cnz, i, j, k);
+      if (own) su[c] = v;
+    }
+  __syncthreads();
+  auto nbsum = [&](int q, int r) {
+    T un[6];
+#pragma unroll
+    for (int a = 0; a < 6; ++a) un[a] = su[nb[q][r][a]];
+    T acc = 0;
+#pragma unroll
+    for (int a = 0; a < 6; ++a) acc = acc + b[q][r][a] * un[a];
+    return acc;
+  };
+  for (int it = 0; it < sweeps; ++it) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const T v = smooth_div(fr[q][r] + nbsum(q, r), dg[q][r]);
+        if (cell[q][r] >= 0) su[cell[q][r]] = v;
       }
       __syncthreads();
     }
-}
-
-// A small level staged in LDS by NT threads, NC cells each (the host checks
-// small_fits_lds and n <= NT NC): the level's coefficient and right-hand side and its
-// correction (plus the prolonged coarse correction if uc_in, zero if zero_u) are
-// loaded once, all loads of a thread in flight together; every sweep runs on the LDS
-// copies with the cell updates of the one-colour launches (same values), and the
-// correction is stored back; with fc_out the level's residual is then restricted to
-// the next coarser level (its correction zeroed), as the restriction launch does.
-template <typename T, int NT, int NC>
-__global__ void __launch_bounds__(NT) k_small_lds(T* u, const T* f, const T* eps, int nx, int ny, int nz,
-                                                 int sweeps, bool zero_u, const T* uc_in, T* fc_out,
-                                                 T* uc_out, int cnx, int cny, int cnz) {
-  extern __shared__ __align__(16) char smem[];
-  const int n = nx * ny * nz;
-  T* su = reinterpret_cast<T*>(smem);
-  T* sf = su + n;
-  T* se = sf + n;
-  T vu[NC], vf[NC], ve[NC];
+  }
 #pragma unroll
-  for (int r = 0; r < NC; ++r) {
-    const int c = (int)threadIdx.x + r * NT;
-    vu[r] = vf[r] = ve[r] = (T)0;
-    if (c < n) {
-      vu[r] = zero_u ? (T)0 : u[c];
-      vf[r] = f[c];
-      ve[r] = eps[c];
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int c = cell[q][r];
+      if (c < 0) continue;
+      const T uc = su[c];
+      u[c] = uc;
+      if (fc_out) sr[c] = fr[q][r] - (dg[q][r] * uc - nbsum(q, r));
     }
-  }
-  if (uc_in) {
-#pragma unroll
-    for (int r = 0; r < NC; ++r) {
-      const int c = (int)threadIdx.x + r * NT;
-      if (c < n) {
-        const int i = c % nx, j = (c / nx) % ny, k = c / (nx * ny);
-        vu[r] = vu[r] + prolong_value<T>(uc_in, cnx, cny, cnz, i, j, k);
-      }
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < NC; ++r) {
-    const int c = (int)threadIdx.x + r * NT;
-    if (c < n) {
-      su[c] = vu[r];
-      sf[c] = vf[r];
-      se[c] = ve[r];
-    }
-  }
-  __syncthreads();
-  if constexpr (sizeof(T) == 4)
-    small_sweeps_cached<T, NT, NC>(su, sf, se, nx, ny, nz, sweeps);
-  else
-    rb_sweeps<T>(su, sf, se, nx, ny, nz, sweeps);
-#pragma unroll
-  for (int r = 0; r < NC; ++r) {
-    const int c = (int)threadIdx.x + r * NT;
-    if (c < n) u[c] = su[c];
-  }
   if (fc_out) {
+    __syncthreads();
     const int cn = cnx * cny * cnz;
     for (int q = threadIdx.x; q < cn; q += NT) {
       const int ci = q % cnx, cj = (q / cnx) % cny, ck = q / (cnx * cny);
-      restrict_cell<T, false>(su, sf, se, nx, ny, nz, fc_out, uc_out, cnx, cny, ci, cj, ck);
+      T s8 = 0;
+#pragma unroll
+      for (int d = 0; d < 8; ++d)
+        s8 += sr[2 * ci + (d & 1) + sy * (2 * cj + ((d >> 1) & 1)) + sz * (2 * ck + (d >> 2))];
+      fc_out[q] = s8 * (T)0.5;
+      uc_out[q] = (T)0;
     }
   }
 }
 
-// Launch of the LDS form on a level of n cells (n <= kSmallLevel, small_fits_lds).
 template <typename T>
-static void launch_small_lds(hipStream_t s, uint32_t n, T* u, const T* f, const T* eps, int nx, int ny,
-                             int nz, int sweeps, bool zero_u, const T* uc_in, T* fc_out, T* uc_out, int cnx,
-                             int cny, int cnz) {
-  const size_t lds = 3 * (size_t)n * sizeof(T);
-  if (n <= 64)
-    k_small_lds<T, 64, 1><<<1, 64, lds, s>>>(u, f, eps, nx, ny, nz, sweeps, zero_u, uc_in, fc_out, uc_out,
-                                             cnx, cny, cnz);
-  else
-    k_small_lds<T, kSmallThreads<T>, kSmallCells<T>><<<1, kSmallThreads<T>, lds, s>>>(
-        u, f, eps, nx, ny, nz, sweeps, zero_u, uc_in, fc_out, uc_out, cnx, cny, cnz);
-}
-
-// Coarsest level: red-black sweeps from zero inside one workgroup (levels too large
-// for the LDS form).
-template <typename T>
-__global__ void __launch_bounds__(1024) k_bottom(T* u, const T* f, const T* eps, int nx, int ny, int nz,
-                                                int sweeps) {
-  const int n = nx * ny * nz;
-  for (int c = threadIdx.x; c < n; c += blockDim.x) u[c] = (T)0;
-  __syncthreads();
-  rb_sweeps<T>(u, f, eps, nx, ny, nz, sweeps);
+static void launch_small_level(hipStream_t s, T* u, const T* f, const T* cf, int nx, int ny, int nz, int sweeps,
+                               bool zero_u, const T* uc_in, T* fc_out, T* uc_out, int cnx, int cny, int cnz) {
+  const int pos = ((nx + 1) / 2) * ny * nz;  // positions of one colour (n <= 4096: at most 4096)
+  const int nr = pos <= 1024 ? 1 : pos <= 2048 ? 2 : 4;
+  const int nt = ((pos + nr - 1) / nr + 63) / 64 * 64;
+  const size_t lds = (size_t)(fc_out ? 2 : 1) * nx * ny * nz * sizeof(T);
+  const auto go = [&](auto kern) {
+    kern<<<1, nt, lds, s>>>(u, f, cf, nx, ny, nz, sweeps, zero_u, uc_in, fc_out, uc_out, cnx, cny, cnz);
+  };
+  if (nt == 64) go(k_small_level<T, 1, 64>);
+  else if (nr == 1 && nt <= 512) go(k_small_level<T, 1, 512>);
+  else if (nr == 1) go(k_small_level<T, 1, 1024>);
+  else if (nr == 2) go(k_small_level<T, 2, 1024>);
+  else go(k_small_level<T, 4, 1024>);
 }
 
 // ---- finest level over row segments ---------------------------------------------------
@@ -1845,6 +1825,9 @@ static int build_levels(const itokmc_grid_desc* d, int dims[kMaxLevels][3]) {
   return nl;
 }
 
+// Levels that run in one workgroup (k_small_level).
+static bool small_level(int l, int nlev, size_t n) { return (l > 0 || nlev == 1) && n <= kSmallLevel; }
+
 size_t field_bytes(const itokmc_grid_desc* d) {
   if (d->field_mode != ITOKMC_FIELD_POISSON) return 0;
   const size_t T = d->precision == ITOKMC_FP64 ? 8 : 4;
@@ -1854,7 +1837,11 @@ size_t field_bytes(const itokmc_grid_desc* d) {
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const size_t npart = (size_t)kRedBlocks > (n + 255) / 256 ? (size_t)kRedBlocks : (n + 255) / 256;
   size_t total = al(n * 8) * 3 + al(n * 4 * T) * 2 + al(n * 8) * 2 + al(8 * (8 + npart));
-  for (int l = 0; l < nl; ++l) total += 3 * al((size_t)dims[l][0] * dims[l][1] * dims[l][2] * T);
+  for (int l = 0; l < nl; ++l) {
+    const size_t m = (size_t)dims[l][0] * dims[l][1] * dims[l][2];
+    total += 3 * al(m * T);
+    if (small_level(l, nl, m)) total += al(4 * m * T);
+  }
   return total;
 }
 
@@ -1891,6 +1878,8 @@ int field_init(itokmc_ctx* ctx, char* base) {
     L.u = p; p += al(L.n * T);
     L.f = p; p += al(L.n * T);
     L.eps = p; p += al(L.n * T);
+    L.cf = nullptr;
+    if (small_level(l, nl, L.n)) { L.cf = p; p += al(4 * (size_t)L.n * T); }
   }
   hipError_t e = hipHostMalloc((void**)&F->host_norms, 64, hipHostMallocMapped | hipHostMallocCoherent);
   if (e == hipSuccess) {
@@ -1988,12 +1977,6 @@ static void smooth(FieldState* F, int l, hipStream_t s, int color, bool from_zer
 // refinement cycle on the finest level with the row-segment smoother).
 template <typename T>
 static void smooth_sweeps(FieldState* F, int l, hipStream_t s, int count, bool from_zero = false) {
-  Level& L = F->lev[l];
-  if (l > 0 && L.n <= kSmallLevel) {
-    if (count > 0)
-      k_sweeps_small<T><<<1, 1024, 0, s>>>((T*)L.u, (const T*)L.f, (const T*)L.eps, L.nx, L.ny, L.nz, count);
-    return;
-  }
   for (int it = 0; it < count; ++it) {
     smooth<T>(F, l, s, 0, from_zero && it == 0);
     smooth<T>(F, l, s, 1);
@@ -2017,24 +2000,22 @@ static void vcycle(itokmc_ctx* ctx, FieldState* F, int l, hipStream_t s) {
   T* u = (T*)L.u;
   const T* f = (const T*)L.f;
   const T* ep = (const T*)L.eps;
+  const T* cf = (const T*)L.cf;
   if (l == F->nlev - 1) {
-    if (small_fits_lds<T>(L.n))
-      launch_small_lds<T>(s, L.n, u, f, ep, L.nx, L.ny, L.nz, bottom_count(ctx, L), true, nullptr, nullptr,
-                          nullptr, 0, 0, 0);
-    else
-      k_bottom<T><<<1, 1024, 0, s>>>(u, f, ep, L.nx, L.ny, L.nz, bottom_count(ctx, L));
+    launch_small_level<T>(s, u, f, cf, L.nx, L.ny, L.nz, bottom_count(ctx, L), true, nullptr, nullptr, nullptr,
+                          0, 0, 0);
     return;
   }
   Level& C = F->lev[l + 1];
-  if (l > 0 && L.n <= kSmallLevel && small_fits_lds<T>(L.n)) {
+  if (cf) {
     // natural order (small levels are never split): smoothing from the zero
     // correction that every restriction leaves, and restriction; the coarser cycle;
     // prolongation and smoothing
-    launch_small_lds<T>(s, L.n, u, f, ep, L.nx, L.ny, L.nz, ctx->tune.mg_pre, true, nullptr, (T*)C.f,
-                        (T*)C.u, C.nx, C.ny, C.nz);
+    launch_small_level<T>(s, u, f, cf, L.nx, L.ny, L.nz, ctx->tune.mg_pre, true, nullptr, (T*)C.f, (T*)C.u,
+                          C.nx, C.ny, C.nz);
     vcycle<T>(ctx, F, l + 1, s);
-    launch_small_lds<T>(s, L.n, u, f, ep, L.nx, L.ny, L.nz, ctx->tune.mg_post, false, (const T*)C.u,
-                        nullptr, nullptr, C.nx, C.ny, C.nz);
+    launch_small_level<T>(s, u, f, cf, L.nx, L.ny, L.nz, ctx->tune.mg_post, false, (const T*)C.u, nullptr,
+                          nullptr, C.nx, C.ny, C.nz);
     return;
   }
   smooth_sweeps<T>(F, l, s, ctx->tune.mg_pre, l == 0 && zero_free_start(ctx, F));
@@ -2181,12 +2162,23 @@ template <typename T>
 static int solve(itokmc_ctx* ctx, FieldState* F) {
   hipStream_t s = ctx->s;
   Level& L0 = F->lev[0];
-  for (int l = 1; l < F->nlev; ++l) {
-    Level& Fl = F->lev[l - 1];
+  SmallLevels S{};
+  const T* ef = nullptr;  // the coefficient above the first small level
+  int above = 0;
+  for (int l = 0; l < F->nlev; ++l) {
     Level& Cl = F->lev[l];
-    k_eps_restrict<T><<<blocks(Cl.n), 256, 0, s>>>((const T*)Fl.eps, Fl.nx, Fl.ny, F->lsplit[l - 1] ? 1 : 0,
-                                                   (T*)Cl.eps, Cl.nx, Cl.ny, Cl.nz, F->lsplit[l] ? 1 : 0);
+    if (Cl.cf) {
+      if (S.count == 0 && l > 0) { ef = (const T*)F->lev[l - 1].eps; above = l - 1; }
+      S.nx[S.count] = Cl.nx; S.ny[S.count] = Cl.ny; S.nz[S.count] = Cl.nz;
+      S.eps[S.count] = Cl.eps; S.cf[S.count] = Cl.cf;
+      ++S.count;
+    } else if (l > 0) {
+      Level& Fl = F->lev[l - 1];
+      k_eps_restrict<T><<<blocks(Cl.n), 256, 0, s>>>((const T*)Fl.eps, Fl.nx, Fl.ny, F->lsplit[l - 1] ? 1 : 0,
+                                                     (T*)Cl.eps, Cl.nx, Cl.ny, Cl.nz, F->lsplit[l] ? 1 : 0);
+    }
   }
+  k_small_setup<T><<<1, 1024, 0, s>>>(S, ef, F->lev[above].nx, F->lev[above].ny, F->lsplit[above] ? 1 : 0);
   const int maxc = ctx->d.gmg_max_cycles > 0 ? ctx->d.gmg_max_cycles : 50;
   ctx->total_solves += 1;
   residual<T>(F, s);
