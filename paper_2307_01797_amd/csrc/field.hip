@@ -43,7 +43,9 @@ struct Level {
   void* u;    // correction
   void* f;    // right-hand side (scaled by h^2)
   void* eps;  // cell coefficient 1 + sigma dt / eps0
-  void* cf;   // small levels: face coefficients and diagonal (k_small_setup)
+  void* cf;   // small levels: packed face coefficients and diagonal; tiled levels in double:
+              // the same as four arrays
+  void* u2;   // tiled levels below the finest: the correction after post-smoothing
 };
 
 struct Coef {
@@ -1139,9 +1141,9 @@ __global__ void __launch_bounds__(128) k_prolong3(T* u, int nx, int ny, int nz, 
 // Levels of at most kSmallLevel cells below the finest (and a single-level grid) run their
 // sweeps in one workgroup with the correction in LDS.  Their face coefficients and
 // diagonals do not change within a solve, so one launch per solve forms them for all of
-// them (k_small_setup: three face coefficients towards the + neighbours and the diagonal
-// per cell; the harmonic mean is symmetric in its two cells, so both read the same
-// value).  In the sweeps a thread owns up to NR cells of each colour and keeps their
+// them (k_small_setup, level_faces: three face coefficients towards the + neighbours and
+// the diagonal per cell; the harmonic mean is symmetric in its two cells, so both read the
+// same value).  In the sweeps a thread owns up to NR cells of each colour and keeps their
 // coefficients, diagonals and right-hand sides in registers: a colour is six LDS reads
 // and the update.  Owning cells by colour keeps every lane of a wavefront at work in each
 // colour.  The arithmetic and its order are op_row's and smooth_div's (a face outside the
@@ -1156,8 +1158,28 @@ struct SmallLevels {
   int count;
   int nx[kMaxLevels], ny[kMaxLevels], nz[kMaxLevels];
   void* eps[kMaxLevels];
-  void* cf[kMaxLevels];  // x, y and z face coefficients and the diagonal, n values each
+  void* cf[kMaxLevels];  // packed (x, y, z face coefficient, diagonal) per cell
 };
+
+// Coefficients of cell (i, j, k) of a level in natural order: its faces towards the +
+// neighbours (zero on the domain boundary) and its diagonal, by op_row's arithmetic.
+template <typename T>
+__device__ __forceinline__ void level_faces(const T* e, int nx, int ny, int nz, int i, int j, int k, T v[4]) {
+  const int sy = nx, sz = nx * ny, c = i + sy * j + sz * k;
+  bool in[6];
+  faces_in(i, j, k, nx, ny, nz, in);
+  const int off[6] = {in[0] ? -1 : 0, in[1] ? 1 : 0, in[2] ? -sy : 0,
+                      in[3] ? sy : 0, in[4] ? -sz : 0, in[5] ? sz : 0};
+  const T ec = e[c];
+  T d = 0;
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    const T b = hmean_s(ec, e[c + off[q]]);
+    d = in[q] ? d + b : (q >= 4 ? d + (T)2 * ec : d);
+    if (q & 1) v[q >> 1] = in[q] ? b : (T)0;
+  }
+  v[3] = d;
+}
 
 // Coefficients of the small levels, finest first, in one workgroup: the cell coefficient
 // of each (restricted from the level above it; the first one from ef unless that is null:
@@ -1165,7 +1187,7 @@ struct SmallLevels {
 template <typename T>
 __global__ void __launch_bounds__(1024) k_small_setup(SmallLevels L, const T* ef, int fnx, int fny, int fsplit) {
   for (int l = 0; l < L.count; ++l) {
-    const int nx = L.nx[l], ny = L.ny[l], nz = L.nz[l], n = nx * ny * nz, sy = nx, sz = nx * ny;
+    const int nx = L.nx[l], ny = L.ny[l], nz = L.nz[l], n = nx * ny * nz, sz = nx * ny;
     T* const e = reinterpret_cast<T*>(L.eps[l]);
     T* const cf = reinterpret_cast<T*>(L.cf[l]);
     if (ef)
@@ -1173,19 +1195,9 @@ __global__ void __launch_bounds__(1024) k_small_setup(SmallLevels L, const T* ef
         e[c] = eps_child_mean<T>(ef, fnx, fny, fsplit, c % nx, (c / nx) % ny, c / sz);
     __syncthreads();
     for (int c = threadIdx.x; c < n; c += 1024) {
-      bool in[6];
-      faces_in(c % nx, (c / nx) % ny, c / sz, nx, ny, nz, in);
-      const int off[6] = {in[0] ? -1 : 0, in[1] ? 1 : 0, in[2] ? -sy : 0,
-                          in[3] ? sy : 0, in[4] ? -sz : 0, in[5] ? sz : 0};
-      const T ec = e[c];
-      T d = 0;
-#pragma unroll
-      for (int q = 0; q < 6; ++q) {
-        const T b = hmean_s(ec, e[c + off[q]]);
-        d = in[q] ? d + b : (q >= 4 ? d + (T)2 * ec : d);
-        if (q & 1) cf[(size_t)(q >> 1) * n + c] = in[q] ? b : (T)0;
-      }
-      cf[(size_t)3 * n + c] = d;
+      T v[4];
+      level_faces<T>(e, nx, ny, nz, c % nx, (c / nx) % ny, c / sz, v);
+      st4<T>(cf + 4 * (size_t)c, v[0], v[1], v[2], v[3]);
     }
     ef = e;
     fnx = nx;
@@ -1225,10 +1237,10 @@ __global__ void __launch_bounds__(MAXT) k_small_level(T* u, const T* f, const T*
       for (int a = 0; a < 6; ++a) {
         nb[q][r][a] = c + off[a];
         // the face below a cell is the + face of its lower neighbour
-        const T v = cf[(size_t)(a >> 1) * n + ((a & 1) ? c : c + off[a])];
+        const T v = cf[4 * (size_t)((a & 1) ? c : c + off[a]) + (a >> 1)];
         b[q][r][a] = in[a] ? v : (T)0;
       }
-      dg[q][r] = cf[(size_t)3 * n + c];
+      dg[q][r] = cf[4 * (size_t)c + 3];
       fr[q][r] = f[c];
       T v = zero_u ? (T)0 : u[c];
       if (uc_in && own) v = v + prolong_value<T>(uc_in, cnx, cny, cnz, i, j, k);
@@ -1295,6 +1307,240 @@ static void launch_small_level(hipStream_t s, T* u, const T* f, const T* cf, int
   else if (nr == 1) go(k_small_level<T, 1, 1024>);
   else if (nr == 2) go(k_small_level<T, 2, 1024>);
   else go(k_small_level<T, 4, 1024>);
+}
+
+// ---- tiled levels ---------------------------------------------------------------------
+// Levels of up to tile_max cells are bound by their launches, not by memory: a colour of a
+// 32^3 or 64^3 level takes the 3.5 us that any launch takes.  Here one launch does a
+// level's whole pre-smoothing (from the zero correction, with the restriction of the
+// residual) or its post-smoothing (with the prolongation): a workgroup takes an 8^3 core
+// with a halo of kHalo cells, whose colours it repeats in LDS.  A cell of the halo is
+// right as long as its distance from the region's edge is at least the number of colours
+// done (pre-smoothing, from known zeros outside: one less), so up to kHalo colours leave
+// the core right (and, for the residual, the ring around it).  A thread owns two cells of
+// each colour, with their coefficients (formed once per solve by k_tile_faces), diagonals
+// and right-hand sides in registers; a cell outside the domain has zero coefficients and
+// stays zero.  The arithmetic and its order are those of the one-colour launches.
+// Single precision, microseconds per cycle (tiled: two launches; one colour each: eight
+// sweeps, restriction, prolongation): 32^3 18 against 45, 64^3 30 against 43, 128^3 225
+// against 57 (the redundant work is 8 region cells per core cell).  Double: 32^3 17 against
+// 64, 64^3 37 against 62, 72x56x88 (finest: with the potential's update) 55 against 67.
+constexpr int kTile = 8, kHalo = 4, kRegion = kTile + 2 * kHalo, kTileLd = kRegion + 2;
+constexpr uint32_t tile_max(size_t T) { return T == 8 ? 1u << 19 : 1u << 18; }  // cells
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_tile_faces(const T* e, int nx, int ny, int nz, T* cf) {
+  const uint32_t n = (uint32_t)nx * ny * nz;
+  for (uint32_t c = blockIdx.x * 256u + threadIdx.x; c < n; c += gridDim.x * 256u) {
+    const uint32_t row = c / (uint32_t)nx, k = row / (uint32_t)ny;
+    T v[4];
+    level_faces<T>(e, nx, ny, nz, (int)(c - row * (uint32_t)nx), (int)(row - k * (uint32_t)ny), (int)k, v);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) cf[(size_t)q * n + c] = v[q];
+  }
+}
+
+// Two neighbouring values of T as one access.
+template <typename T>
+__device__ __forceinline__ void ld2(const T* p, T v[2]) {
+  if constexpr (sizeof(T) == 4) {
+    const float2 x = *reinterpret_cast<const float2*>(p);
+    v[0] = x.x; v[1] = x.y;
+  } else {
+    const double2 x = *reinterpret_cast<const double2*>(p);
+    v[0] = x.x; v[1] = x.y;
+  }
+}
+
+// kPost: u + the prolonged coarse correction uc, then the sweeps, into `out` (another
+// array than u, whose halo the neighbouring workgroups read) or, on the finest level,
+// added to the potential phi.  Otherwise: the sweeps from zero into u, and the coarse
+// right-hand side fc.
+// A thread owns the cells (2m, 2m + 1) of a row in two planes z and z + 8: one cell of
+// each colour in each pair, loaded together (the levels' rows are even, as they are
+// coarsened).  Single precision forms the face coefficients from the cell coefficients
+// staged in LDS (the hardware reciprocal is cheaper than the halo's traffic); double reads
+// the ones k_tile_faces has formed (no division here).  A wavefront's cells lie in one
+// plane: the planes that no longer matter for the core are skipped colour by colour.
+template <typename T, bool kPost>
+__global__ void __launch_bounds__(1024) k_tile_level(T* u, const T* f, const T* eps, const T* cf, int nx, int ny,
+                                                     int nz, int sweeps, const T* uc, int cnx, int cny, int cnz,
+                                                     T* out, double* phi, T* fc) {
+  constexpr int kLy = kTileLd, kLz = kTileLd * kTileLd, kAll = kTileLd * kLz;
+  constexpr int kC = kRegion / 2 + 2, kCy = kC, kCz = kC * kC;  // coarse cells under the region
+  __shared__ T su[kAll];
+  // post: the coarse correction; pre: the residual of the core
+  __shared__ T sx[kPost ? kC * kCz : kTile * kTile * kTile];
+  const int tx = (nx + kTile - 1) / kTile, ty = (ny + kTile - 1) / kTile;
+  const int tile = (int)xcd_block(blockIdx.x, gridDim.x);
+  const int bz = tile / (tx * ty), by = (tile - bz * tx * ty) / tx, bx = tile - (bz * ty + by) * tx;
+  const int x0 = bx * kTile - kHalo, y0 = by * kTile - kHalo, z0 = bz * kTile - kHalo;
+  const int sy = nx, sz = nx * ny;
+  const int m = (int)threadIdx.x & 7, y = (int)(threadIdx.x >> 3) & 15, zb = (int)(threadIdx.x >> 7);
+  const int i = x0 + 2 * m, j = y0 + y;  // the pair's first cell
+  if constexpr (sizeof(T) == 4) {
+    for (int t = (int)threadIdx.x; t < kAll; t += 1024) {
+      const int lz = t / kLz, ly = (t - lz * kLz) / kLy, lx = t - lz * kLz - ly * kLy;
+      const int ei = min(max(x0 + lx - 1, 0), nx - 1), ej = min(max(y0 + ly - 1, 0), ny - 1),
+                ek = min(max(z0 + lz - 1, 0), nz - 1);
+      su[t] = eps[ei + sy * ej + sz * ek];
+    }
+  }
+  if constexpr (kPost) {
+    // a coarse value past a Neumann face is its cell's, past a Dirichlet face its negative
+    // (prolong_value's rules; the sign is exact)
+    const int cx0 = (x0 >> 1) - 1, cy0 = (y0 >> 1) - 1, cz0 = (z0 >> 1) - 1;
+    if (threadIdx.x < (unsigned)(kC * kCz)) {
+      const int lz = (int)threadIdx.x / kCz, ly = ((int)threadIdx.x - lz * kCz) / kCy,
+                lx = (int)threadIdx.x - lz * kCz - ly * kCy;
+      const int ci = min(max(cx0 + lx, 0), cnx - 1), cj = min(max(cy0 + ly, 0), cny - 1), kk = cz0 + lz;
+      const T v = uc[ci + (size_t)cnx * (cj + (size_t)cny * min(max(kk, 0), cnz - 1))];
+      sx[threadIdx.x] = kk < 0 || kk >= cnz ? -v : v;
+    }
+  }
+  T b[2][2][6], dg[2][2], fr[2][2], v0[2][2];  // [colour][plane]
+  int at[2][2];                                // LDS position
+  bool own[2];
+  if constexpr (sizeof(T) == 4) __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int z = zb + 8 * r, k = z0 + z;
+    own[r] = i >= 0 && i < nx && j >= 0 && j < ny && k >= 0 && k < nz;  // the whole pair
+    const int c = own[r] ? i + sy * j + sz * k : 0;
+    T ff[2], uu[2] = {(T)0, (T)0}, bp[2][6], dp[2];
+    ld2<T>(f + c, ff);
+    if constexpr (kPost) ld2<T>(u + c, uu);
+    if constexpr (sizeof(T) == 4) {
+      const T* e = su + (2 * m + 1) + kLy * (y + 1) + kLz * (z + 1);
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        bool in[6];
+        faces_in(i + a, j, k, nx, ny, nz, in);
+        const T* p = e + a;
+        const T en[6] = {p[-1], p[1], p[-kLy], p[kLy], p[-kLz], p[kLz]};
+        T d = 0;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+          const T w = hmean_s(p[0], en[q]);
+          d = in[q] ? d + w : (q >= 4 ? d + (T)2 * p[0] : d);
+          bp[a][q] = in[q] ? w : (T)0;
+        }
+        dp[a] = d;
+      }
+    } else {
+      const size_t n = (size_t)sz * nz;
+      const bool ym = own[r] && j > 0, zm = own[r] && k > 0;
+      T fx[2], fy[2], fz[2], gy[2], gz[2];
+      const T gx = cf[own[r] && i > 0 ? c - 1 : c];
+      ld2<T>(cf + c, fx);
+      ld2<T>(cf + n + c, fy);
+      ld2<T>(cf + n + (ym ? c - sy : c), gy);
+      ld2<T>(cf + 2 * n + c, fz);
+      ld2<T>(cf + 2 * n + (zm ? c - sz : c), gz);
+      ld2<T>(cf + 3 * n + c, dp);
+      bp[0][0] = i > 0 ? gx : (T)0; bp[0][1] = fx[0];
+      bp[1][0] = fx[0];             bp[1][1] = fx[1];
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        bp[a][2] = ym ? gy[a] : (T)0; bp[a][3] = fy[a];
+        bp[a][4] = zm ? gz[a] : (T)0; bp[a][5] = fz[a];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      // the region's origin is even in every axis: local and global colours agree
+      const int a = (y + z + q) & 1;
+      at[q][r] = (2 * m + a + 1) + kLy * (y + 1) + kLz * (z + 1);
+#pragma unroll
+      for (int w = 0; w < 6; ++w) b[q][r][w] = own[r] ? (a ? bp[1][w] : bp[0][w]) : (T)0;
+      dg[q][r] = own[r] ? (a ? dp[1] : dp[0]) : (T)1;
+      fr[q][r] = own[r] ? (a ? ff[1] : ff[0]) : (T)0;
+      v0[q][r] = own[r] ? (a ? uu[1] : uu[0]) : (T)0;
+    }
+  }
+  if constexpr (sizeof(T) == 4) __syncthreads();  // the coefficients are read
+  for (int t = (int)threadIdx.x; t < kAll; t += 1024) su[t] = (T)0;
+  __syncthreads();
+  if constexpr (kPost) {
+    const T wt[2] = {(T)0.75, (T)0.25};
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const int z = zb + 8 * r, x = 2 * m + ((y + z + q) & 1);
+        // the nearer coarse centre and the step to the farther one, along each axis
+        const T* p = sx + ((x >> 1) + 1) + kCy * ((y >> 1) + 1) + kCz * ((z >> 1) + 1);
+        const int ox = (x & 1) ? 1 : -1, oy = (y & 1) ? kCy : -kCy, oz = (z & 1) ? kCz : -kCz;
+        T acc = 0;
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+          acc += wt[c & 1] * wt[(c >> 1) & 1] * wt[c >> 2] *
+                 p[((c & 1) ? ox : 0) + ((c & 2) ? oy : 0) + ((c & 4) ? oz : 0)];
+        if (own[r]) su[at[q][r]] = v0[q][r] + acc;
+      }
+    __syncthreads();
+  }
+  auto nbsum = [&](int q, int r) {
+    const T* p = su + at[q][r];
+    const T un[6] = {p[-1], p[1], p[-kLy], p[kLy], p[-kLz], p[kLz]};
+    T acc = 0;
+#pragma unroll
+    for (int a = 0; a < 6; ++a) acc = acc + b[q][r][a] * un[a];
+    return acc;
+  };
+  int edge = kPost ? 1 : 0;  // planes nearer to the region's edge than this have gone wrong
+  for (int it = 0; it < sweeps; ++it) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const int z = zb + 8 * r;
+        if (z >= edge && z < kRegion - edge) su[at[q][r]] = smooth_div(fr[q][r] + nbsum(q, r), dg[q][r]);
+      }
+      ++edge;
+      __syncthreads();
+    }
+  }
+  const int cx = 2 * m - kHalo, cy = y - kHalo;
+  const bool core = cx >= 0 && cx < kTile && cy >= 0 && cy < kTile;
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const int z = zb + 8 * r, cz = z - kHalo;
+    if (!core || cz < 0 || cz >= kTile) continue;
+    const size_t c = (size_t)i + (size_t)sy * j + (size_t)sz * (z0 + z);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int a = (y + z + q) & 1;
+      const T v = su[at[q][r]];
+      if constexpr (kPost) {
+        if (own[r]) {
+          if (phi) phi[c + a] += (double)v;
+          else out[c + a] = v;
+        }
+      } else {
+        if (own[r]) u[c + a] = v;
+        sx[cx + a + kTile * (cy + kTile * cz)] = fr[q][r] - (dg[q][r] * v - nbsum(q, r));
+      }
+    }
+  }
+  if constexpr (!kPost) {
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      const int x = (int)threadIdx.x & 3, yy = ((int)threadIdx.x >> 2) & 3, z = (int)threadIdx.x >> 4;
+      const int ci = bx * 4 + x, cj = by * 4 + yy, ck = bz * 4 + z;
+      if (ci < cnx && cj < cny && ck < cnz) {
+        T s8 = 0;
+#pragma unroll
+        for (int d = 0; d < 8; ++d)
+          s8 += sx[2 * x + (d & 1) + kTile * (2 * yy + ((d >> 1) & 1) + kTile * (2 * z + (d >> 2)))];
+        fc[(size_t)ci + (size_t)cnx * ((size_t)cj + (size_t)cny * ck)] = s8 * (T)0.5;
+      }
+    }
+  }
+}
+
+static int tile_blocks(int nx, int ny, int nz) {
+  return ((nx + kTile - 1) / kTile) * ((ny + kTile - 1) / kTile) * ((nz + kTile - 1) / kTile);
 }
 
 // ---- finest level over row segments ---------------------------------------------------
@@ -1801,6 +2047,7 @@ struct FieldState {
   // kSmallLevel cells takes both when the finest level is split.
   bool lsplit[kMaxLevels] = {};
   bool lseg[kMaxLevels] = {};
+  bool ltile[kMaxLevels] = {};  // k_tile_level (natural order)
   bool graph_failed = false;
   hipGraphExec_t graph_exec = nullptr;
   // optional timing of the finest-level smoother launches: event pairs recorded around
@@ -1827,6 +2074,11 @@ static int build_levels(const itokmc_grid_desc* d, int dims[kMaxLevels][3]) {
 
 // Levels that run in one workgroup (k_small_level).
 static bool small_level(int l, int nlev, size_t n) { return (l > 0 || nlev == 1) && n <= kSmallLevel; }
+// Levels that can run in tiles (k_tile_level): every one above the coarsest that is not
+// small.
+static bool tile_level(int l, int nlev, size_t n, size_t T) {
+  return l < nlev - 1 && !small_level(l, nlev, n) && n <= tile_max(T);
+}
 
 size_t field_bytes(const itokmc_grid_desc* d) {
   if (d->field_mode != ITOKMC_FIELD_POISSON) return 0;
@@ -1840,7 +2092,8 @@ size_t field_bytes(const itokmc_grid_desc* d) {
   for (int l = 0; l < nl; ++l) {
     const size_t m = (size_t)dims[l][0] * dims[l][1] * dims[l][2];
     total += 3 * al(m * T);
-    if (small_level(l, nl, m)) total += al(4 * m * T);
+    if (small_level(l, nl, m) || (T == 8 && tile_level(l, nl, m, T))) total += al(4 * m * T);
+    if (tile_level(l, nl, m, T) && l > 0) total += al(m * T);
   }
   return total;
 }
@@ -1879,7 +2132,9 @@ int field_init(itokmc_ctx* ctx, char* base) {
     L.f = p; p += al(L.n * T);
     L.eps = p; p += al(L.n * T);
     L.cf = nullptr;
-    if (small_level(l, nl, L.n)) { L.cf = p; p += al(4 * (size_t)L.n * T); }
+    L.u2 = nullptr;
+    if (small_level(l, nl, L.n) || (T == 8 && tile_level(l, nl, L.n, T))) { L.cf = p; p += al(4 * (size_t)L.n * T); }
+    if (tile_level(l, nl, L.n, T) && l > 0) { L.u2 = p; p += al(L.n * T); }
   }
   hipError_t e = hipHostMalloc((void**)&F->host_norms, 64, hipHostMallocMapped | hipHostMallocCoherent);
   if (e == hipSuccess) {
@@ -1993,6 +2248,12 @@ static int bottom_count(const itokmc_ctx* ctx, const Level& L) {
   return ctx->tune.bottom_sweeps > 0 ? ctx->tune.bottom_sweeps : 4 * mx + 16;
 }
 
+// Where level l's correction is after its part of the cycle.
+template <typename T>
+static T* correction(FieldState* F, int l) {
+  return (T*)(F->ltile[l] && l > 0 ? F->lev[l].u2 : F->lev[l].u);
+}
+
 // V-cycle from level l.
 template <typename T>
 static void vcycle(itokmc_ctx* ctx, FieldState* F, int l, hipStream_t s) {
@@ -2007,15 +2268,25 @@ static void vcycle(itokmc_ctx* ctx, FieldState* F, int l, hipStream_t s) {
     return;
   }
   Level& C = F->lev[l + 1];
-  if (cf) {
+  if (F->ltile[l]) {
+    const int nt = tile_blocks(L.nx, L.ny, L.nz);
+    k_tile_level<T, false><<<nt, 1024, 0, s>>>(u, f, ep, cf, L.nx, L.ny, L.nz, ctx->tune.mg_pre, nullptr, C.nx, C.ny,
+                                               C.nz, nullptr, nullptr, (T*)C.f);
+    vcycle<T>(ctx, F, l + 1, s);
+    k_tile_level<T, true><<<nt, 1024, 0, s>>>(u, f, ep, cf, L.nx, L.ny, L.nz, ctx->tune.mg_post,
+                                              correction<T>(F, l + 1), C.nx, C.ny, C.nz, (T*)L.u2,
+                                              l == 0 ? F->phi : nullptr, nullptr);
+    return;
+  }
+  if (small_level(l, F->nlev, L.n)) {
     // natural order (small levels are never split): smoothing from the zero
     // correction that every restriction leaves, and restriction; the coarser cycle;
     // prolongation and smoothing
     launch_small_level<T>(s, u, f, cf, L.nx, L.ny, L.nz, ctx->tune.mg_pre, true, nullptr, (T*)C.f, (T*)C.u,
                           C.nx, C.ny, C.nz);
     vcycle<T>(ctx, F, l + 1, s);
-    launch_small_level<T>(s, u, f, cf, L.nx, L.ny, L.nz, ctx->tune.mg_post, false, (const T*)C.u, nullptr,
-                          nullptr, C.nx, C.ny, C.nz);
+    launch_small_level<T>(s, u, f, cf, L.nx, L.ny, L.nz, ctx->tune.mg_post, false,
+                          correction<T>(F, l + 1), nullptr, nullptr, C.nx, C.ny, C.nz);
     return;
   }
   smooth_sweeps<T>(F, l, s, ctx->tune.mg_pre, l == 0 && zero_free_start(ctx, F));
@@ -2035,7 +2306,7 @@ static void vcycle(itokmc_ctx* ctx, FieldState* F, int l, hipStream_t s) {
     k_restrict3<T, false><<<gr, 128, 0, s>>>(u, f, ep, L.nx, L.ny, L.nz, fcp, ucp, C.nx, C.ny);
   }
   vcycle<T>(ctx, F, l + 1, s);
-  const T* ucc = (const T*)C.u;
+  const T* ucc = correction<T>(F, l + 1);
   if (F->lseg[l]) {
     if (fs && csp) k_prolong_seg<T, true, true><<<sb, 256, 0, s>>>(u, L.nx, L.ny, L.nz, ucc, C.nx, C.ny, C.nz);
     else if (fs) k_prolong_seg<T, true, false><<<sb, 256, 0, s>>>(u, L.nx, L.ny, L.nz, ucc, C.nx, C.ny, C.nz);
@@ -2118,11 +2389,13 @@ static void refine_cycle(itokmc_ctx* ctx, FieldState* F, hipStream_t s) {
   F->sm_n = 0;
   // the correction starts at zero; the first colour-0 sweep can assume it instead (the
   // colour-1 sweep that follows writes the rest of the level before anything reads it)
-  if (!zero_free_start(ctx, F)) k_zero<T><<<blocks(L0.n), 256, 0, s>>>((T*)L0.u, L0.n);
+  if (!F->ltile[0] && !zero_free_start(ctx, F)) k_zero<T><<<blocks(L0.n), 256, 0, s>>>((T*)L0.u, L0.n);
   vcycle<T>(ctx, F, 0, s);
   const dim3 gp = row_grid(L0.nx, L0.ny, L0.nz);
   const int sb = seg_blocks(L0.nx, L0.ny, L0.nz);
-  if (F->seg && F->split)
+  if (F->ltile[0]) {
+    // the last tiled launch has added the correction to the potential
+  } else if (F->seg && F->split)
     k_phi_update_seg<T, true><<<sb, 256, 0, s>>>(F->phi, (const T*)L0.u, L0.nx, L0.ny, L0.nz);
   else if (F->seg)
     k_phi_update_seg<T, false><<<sb, 256, 0, s>>>(F->phi, (const T*)L0.u, L0.nx, L0.ny, L0.nz);
@@ -2167,7 +2440,7 @@ static int solve(itokmc_ctx* ctx, FieldState* F) {
   int above = 0;
   for (int l = 0; l < F->nlev; ++l) {
     Level& Cl = F->lev[l];
-    if (Cl.cf) {
+    if (small_level(l, F->nlev, Cl.n)) {
       if (S.count == 0 && l > 0) { ef = (const T*)F->lev[l - 1].eps; above = l - 1; }
       S.nx[S.count] = Cl.nx; S.ny[S.count] = Cl.ny; S.nz[S.count] = Cl.nz;
       S.eps[S.count] = Cl.eps; S.cf[S.count] = Cl.cf;
@@ -2177,6 +2450,11 @@ static int solve(itokmc_ctx* ctx, FieldState* F) {
       k_eps_restrict<T><<<blocks(Cl.n), 256, 0, s>>>((const T*)Fl.eps, Fl.nx, Fl.ny, F->lsplit[l - 1] ? 1 : 0,
                                                      (T*)Cl.eps, Cl.nx, Cl.ny, Cl.nz, F->lsplit[l] ? 1 : 0);
     }
+  }
+  for (int l = 0; l < F->nlev && sizeof(T) == 8; ++l) {
+    Level& Cl = F->lev[l];
+    if (F->ltile[l])
+      k_tile_faces<T><<<blocks(Cl.n), 256, 0, s>>>((const T*)Cl.eps, Cl.nx, Cl.ny, Cl.nz, (T*)Cl.cf);
   }
   k_small_setup<T><<<1, 1024, 0, s>>>(S, ef, F->lev[above].nx, F->lev[above].ny, F->lsplit[above] ? 1 : 0);
   const int maxc = ctx->d.gmg_max_cycles > 0 ? ctx->d.gmg_max_cycles : 50;
@@ -2213,7 +2491,10 @@ template <typename T>
 static int deposit_and_solve(itokmc_ctx* ctx, FieldState* F, const StepConst& K, int mode) {
   hipStream_t s = ctx->s;
   const uint32_t n = ctx->ncell;
-  const bool split = ctx->tune.fine_layout == 0 && F->nlev > 1;
+  // levels that run in tiles (their colours have to fit the halo) keep natural order
+  const bool tiled = ctx->tune.mg_pre >= 1 && 2 * ctx->tune.mg_pre <= kHalo && 2 * ctx->tune.mg_post <= kHalo;
+  for (int l = 0; l < F->nlev; ++l) F->ltile[l] = tiled && tile_level(l, F->nlev, F->lev[l].n, sizeof(T));
+  const bool split = ctx->tune.fine_layout == 0 && F->nlev > 1 && !F->ltile[0];
   if (split != F->split) {
     field_reset_graph(ctx);
     F->split = split;
@@ -2224,7 +2505,8 @@ static int deposit_and_solve(itokmc_ctx* ctx, FieldState* F, const StepConst& K,
       F->lsplit[0] = F->split;
       F->lseg[0] = F->seg;
     } else {
-      F->lseg[l] = F->lsplit[l] = F->split && l < F->nlev - 1 && L.nx % 8 == 0 && L.n > kSmallLevel;
+      F->lseg[l] = F->lsplit[l] =
+          F->split && l < F->nlev - 1 && L.nx % 8 == 0 && L.n > kSmallLevel && !F->ltile[l];
     }
   }
   phase_begin(ctx, PH_FIELD_PREP);
