@@ -227,6 +227,28 @@ __device__ __forceinline__ uint32_t wave_max_u32_dpp(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)x[0], 63);
 }
 
+// Wavefront minimum and maximum of unsigned values (every lane active; uniform result), by
+// the shifts of wave_prefix_dpp: a lane without a source takes the identity.
+template <typename U, typename Op>
+__device__ __forceinline__ U wave_reduce_dpp(U v, U id, Op op) {
+  v = op(dpp_move<0x111, 0xF, U>(v, id), v);
+  v = op(dpp_move<0x112, 0xF, U>(v, id), v);
+  v = op(dpp_move<0x114, 0xF, U>(v, id), v);
+  v = op(dpp_move<0x118, 0xF, U>(v, id), v);
+  v = op(dpp_move<0x142, 0xA, U>(v, id), v);
+  v = op(dpp_move<0x143, 0xC, U>(v, id), v);
+  if constexpr (sizeof(U) == 8) return (U)lane_u64((uint64_t)v, 63);
+  else return (U)lane_u32((uint32_t)v, 63);
+}
+template <typename U>
+__device__ __forceinline__ U wave_min_dpp(U v) {
+  return wave_reduce_dpp(v, (U)~(U)0, [](U a, U b) { return a < b ? a : b; });
+}
+template <typename U>
+__device__ __forceinline__ U wave_max_dpp(U v) {
+  return wave_reduce_dpp(v, (U)0, [](U a, U b) { return a > b ? a : b; });
+}
+
 // Binning of one particle per lane into acc[key] = (count << 32) | weight (inactive
 // lanes use kInvalidCell): one 64-bit atomic per run of equal consecutive keys, as
 // run_add, but only the count is returned: each active lane's rank in its cell (0 for

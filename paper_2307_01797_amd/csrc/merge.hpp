@@ -53,15 +53,11 @@ template <> struct Bits<double> {
   static constexpr U lo_init = ~0ull;
 };
 
-// The small path also stages the sort keys of splitting leaves contiguously.
+// The small paths stage the sort keys of splitting leaves contiguously and order them by
+// the coordinate alone: equal coordinates, which the ids would order, are rare and show as
+// a collision of two ranks.  Only then are the pieces' ids fetched and ranked (once per
+// cell), so that no id is staged or compared otherwise.
 template <int CAP> struct MergeContig { static constexpr bool value = CAP <= kMergeSmall; };
-
-// In single precision the contiguous path orders pieces by one 64-bit integer: the
-// coordinate's bit pattern (ordered like the non-negative value) above the rank of the
-// piece's id among the cell's pieces, i.e. by (coordinate, id).
-template <typename T, int CAP> struct MergePacked {
-  static constexpr bool value = MergeContig<CAP>::value && sizeof(T) == 4;
-};
 
 // Index of a store entry in the two index buffers: one byte when the store has at most
 // 256 entries (the common staging), else two.
@@ -74,26 +70,16 @@ template <typename T, int CAP, int NL = kMaxMergePpc>
 constexpr size_t merge_lds_bytes_c() {
   constexpr size_t S = (size_t)CAP + NL;
   constexpr size_t U = sizeof(typename Bits<T>::U);
-  return S * ((MergePacked<T, CAP>::value ? 0 : 8) + 3 * sizeof(T) + 4 +
-              2 * sizeof(typename MergeIdx<CAP, NL>::type) + 3)
-                            // store (ids in the contiguous array when packed), two index buffers,
-                            // three tag arrays
-         + (MergeContig<CAP>::value ? S * 8 : 0)               // contiguous ids (packed: keys)
-         + (MergeContig<CAP>::value && !MergePacked<T, CAP>::value ? S * sizeof(T) : 0)  // keys
-         + (MergePacked<T, CAP>::value ? S * sizeof(typename MergeIdx<CAP, NL>::type) : 0)  // id ranks
+  return S * (3 * sizeof(T) + 4 + 2 * sizeof(typename MergeIdx<CAP, NL>::type) + 3)
+                            // store, two index buffers, three tag arrays
+         // small paths: keys, and the source (later the id rank) of a piece; else the ids
+         + S * (MergeContig<CAP>::value ? sizeof(T) + 2 : 8)
          + NL * (2 * 4 + 4 + 6 * U + 1 +                           // weights, extents, axis
                  6 * sizeof(typename MergeIdx<CAP, NL>::type))      // starts, counts, regions,
                                                                     // median positions
          + 64;
 }
 inline int merge_leaves(int n_ppc) { return n_ppc <= 32 ? 32 : kMaxMergePpc; }
-
-// (coordinate, id rank) as one ordered integer (single precision; -0 folds to +0).
-__device__ __forceinline__ uint64_t packed_key(float k, uint32_t r) {
-  return ((uint64_t)__float_as_uint(k + 0.0f) << 32) | r;
-}
-__device__ __forceinline__ uint64_t packed_key(double, uint32_t) { return 0; }
-
 
 __device__ __forceinline__ uint64_t lanemask_lt() {
   const int lane = lane_id();
@@ -116,10 +102,7 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
   const int lane = lane_id();
   char* p = smem;
   constexpr bool contig = MergeContig<CAP>::value;
-  constexpr bool packed = MergePacked<T, CAP>::value;
-  // piece ids: needed by the packed path only until the id ranks are known, so there
-  // they live in the contiguous key array, which is filled later
-  uint64_t* sid_own = (uint64_t*)p; p += packed ? 0 : (size_t)S * 8;
+  uint64_t* sid = (uint64_t*)p; p += contig ? 0 : (size_t)S * 8;  // piece ids (large staging)
   U* lo = (U*)p; p += (size_t)NL * 3 * sizeof(U);
   U* hi = (U*)p; p += (size_t)NL * 3 * sizeof(U);
   // Arrays selected by a run-time index (axis, buffer) are addressed from one base, so
@@ -143,11 +126,12 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
   auto tag = [tagB](int k) { return tagB + (size_t)k * S; };
   uint8_t* otag = (uint8_t*)p; p += (size_t)S;   // splitting leaf owning an ordered slot
   uint8_t* axis = (uint8_t*)p; p += NL;
+  // small paths: where a piece came from (its index in the gather; after a tie, the rank of
+  // its id among the cell's pieces), and the sort key of slot q
+  p = smem + ((size_t)(p - smem) + 1) / 2 * 2;
+  uint16_t* src = (uint16_t*)p; p += contig ? (size_t)S * 2 : 0;
   p = smem + ((size_t)(p - smem) + 15) / 16 * 16;  // stays an LDS address (LDS instructions)
-  uint64_t* kid = (uint64_t*)p; p += contig ? (size_t)S * 8 : 0;   // id (packed: key) of slot q
-  uint64_t* const sid = packed ? kid : sid_own;
-  T* kkey = (T*)p; p += contig && !packed ? (size_t)S * sizeof(T) : 0;  // key of slot q
-  Ix* idr = (Ix*)p; p += packed ? (size_t)S * sizeof(Ix) : 0;   // id rank of store entry
+  T* kkey = (T*)p; p += contig ? (size_t)S * sizeof(T) : 0;
 
   // ---- gather: segment [s, e) then product slots [base, base + M) ----
   uint32_t m = 0, wmax = 0;
@@ -162,14 +146,14 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
     const bool made = gen && qi >= nseg;  // a product made here, not read
     const uint32_t qc = inr && !made ? q : 0u;
     uint32_t wq = b.w[qc];
-    uint64_t iq = b.id[qc];
+    uint64_t iq = contig ? 0ull : b.id[qc];
     T x0 = reinterpret_cast<const T*>(b.ox)[qc];
     T x1 = reinterpret_cast<const T*>(b.oy)[qc];
     T x2 = reinterpret_cast<const T*>(b.oz)[qc];
     if (made && inr) {
       const Product<T> pr = make_product<T>(c, qi - nseg, wb, wr, K.step, K.key);
       wq = pr.w;
-      iq = pr.id;
+      if (!contig) iq = pr.id;
       x0 = pr.o[0];
       x1 = pr.o[1];
       x2 = pr.o[2];
@@ -180,7 +164,8 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
     const uint32_t pos = m + (uint32_t)__popcll(mask & lanemask_lt());
     if (alive) {
       if (pos < (uint32_t)CAP) {
-        sid[pos] = iq;
+        if (contig) src[pos] = (uint16_t)qi;
+        else sid[pos] = iq;
         so(0)[pos] = x0;
         so(1)[pos] = x1;
         so(2)[pos] = x2;
@@ -197,21 +182,16 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
   Wtot = wave_sum64_dpp(Wtot);
   const bool trigger = m > (uint32_t)n_ppc || (m < (uint32_t)n_ppc && wmax >= 2);
   if (!trigger || m == 0) return 0;
-  if (m > (uint32_t)CAP) return 2;
+  if (m > (uint32_t)CAP || (contig && nseg + M > 0x10000u)) return 2;  // (src is 16 bits)
   if (lane == 0) { Lst(0)[0] = 0; Lcn(0)[0] = m; LW(0)[0] = (uint32_t)Wtot; }
   wave_lds_sync();
-  if (packed) {  // rank of every piece's id among the cell's pieces (ids are distinct here)
-    for (uint32_t q = (uint32_t)lane; q < m; q += 64) {
-      const uint64_t iq = sid[q];
-      uint32_t r = 0, t = 0;
-      for (; t + 4 <= m; t += 4)
-        r += (sid[t] < iq ? 1u : 0u) + (sid[t + 1] < iq ? 1u : 0u) + (sid[t + 2] < iq ? 1u : 0u) +
-             (sid[t + 3] < iq ? 1u : 0u);
-      for (; t < m; ++t) r += sid[t] < iq ? 1u : 0u;
-      idr[q] = r;
-    }
-    wave_lds_sync();
-  }
+  // Id of the piece gathered as number qi (small paths; the bank is unchanged until the
+  // leaves are written).
+  auto id_of = [&](uint32_t qi) -> uint64_t {
+    if (qi < nseg) return b.id[s + qi];
+    return gen ? make_id(KIND_KMC, K.step, c, qi - nseg) : b.id[base + (qi - nseg)];
+  };
+  bool ranked = false;  // src holds id ranks
 
   // ---- breadth-first growth, all leaves of a level at once ----
   int cb = 0, nl = 1;
@@ -238,12 +218,15 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
     const uint64_t chm = __ballot(chosen);
     const uint32_t n_i = lane < nl ? Lcn(cb)[lane] : 0u;
     // new leaf index and region of each old leaf (a splitting leaf gets a spare slot)
+    // (three prefixes in one word: leaves, at most 64, region slots and the splitting
+    // leaves' pieces, each below 2^12)
     const uint32_t widx = lane < nl ? (chosen ? 2u : 1u) : 0u;
     const uint32_t wreg = n_i + (chosen ? 1u : 0u);
-    const uint32_t xi = wave_prefix_dpp(widx), xr = wave_prefix_dpp(wreg);
-    const uint32_t newidx = xi - widx, R = xr - wreg;
-    const int nl_new = (int)lane_u32(xi, 63);
-    const uint32_t new_extent = lane_u32(xr, 63);
+    const uint32_t xs3 = wave_prefix_dpp(widx | (wreg << 8) | (chosen ? n_i << 20 : 0u));
+    const uint32_t newidx = (xs3 & 0xFFu) - widx, R = ((xs3 >> 8) & 0xFFFu) - wreg;
+    const uint32_t tot3 = lane_u32(xs3, 63);
+    const int nl_new = (int)(tot3 & 0xFFu);
+    const uint32_t new_extent = (tot3 >> 8) & 0xFFFu, nsplit = tot3 >> 20;
     if (lane < nl) {
       Rg[lane] = R;
       if (chosen) {
@@ -254,34 +237,54 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
     }
     for (uint32_t q = (uint32_t)lane; q < new_extent; q += 64) { tag(ncb)[q] = kNone; otag[q] = kNone; }
     wave_lds_sync();
-    // (i) extents of the splitting leaves: a segmented min/max over each 64-slot chunk
-    // of the buffer (a leaf's slots are contiguous), then one LDS atomic per leaf
-    // segment and bound (LDS atomics of many lanes on one address serialise)
-    for (uint32_t q0 = 0; q0 < extent; q0 += 64) {
-      const uint32_t q = q0 + (uint32_t)lane;
-      const uint8_t L = q < extent ? tag(cb)[q] : kNone;
-      const bool part = L != kNone && ((chm >> L) & 1ull);
-      const uint32_t key = part ? (uint32_t)L : 0xFFFFFFFFu;
-      U mn[3], mx[3];
-      if (part) {
+    // (i) extents of the splitting leaves.  The root's are a plain wavefront reduction (one
+    // DPP minimum or maximum per step, no segments).  Below it, a segmented min/max over
+    // each 64-slot chunk of the buffer (a leaf's slots are contiguous), then one LDS atomic
+    // per leaf segment and bound: LDS atomics of many lanes on one address serialise (one
+    // per piece from four leaves on: 7.8 against 7.2 ms near the particle cap).
+    if (nl == 1) {
+      U ext[6] = {Bits<T>::lo_init, Bits<T>::lo_init, Bits<T>::lo_init, 0, 0, 0};
+      for (uint32_t q = (uint32_t)lane; q < extent; q += 64) {
         const uint16_t pq = I(cb)[q];
-        for (int a = 0; a < 3; ++a) mn[a] = mx[a] = Bits<T>::of(so(a)[pq]);
-      } else {
-        for (int a = 0; a < 3; ++a) { mn[a] = Bits<T>::lo_init; mx[a] = 0; }
-      }
-      // segmented min and max of each axis over the chunk (DPP moves, no LDS)
-      const uint32_t prev = dpp_from_prev(key, ~key);
-      U ext[6] = {mn[0], mn[1], mn[2], mx[0], mx[1], mx[2]};
-      const U eid[6] = {Bits<T>::lo_init, Bits<T>::lo_init, Bits<T>::lo_init, 0, 0, 0};
-      seg_scan(ext, prev != key ? 1u : 0u, eid,
-               [](int k, U a, U b) { return k < 3 ? (a < b ? a : b) : (a > b ? a : b); });
 #pragma unroll
-      for (int a = 0; a < 3; ++a) { mn[a] = ext[a]; mx[a] = ext[3 + a]; }
-      const uint32_t next = dpp_from_next(key, ~key);
-      if (part && (lane == 63 || next != key)) {
         for (int a = 0; a < 3; ++a) {
-          atomicMin(&lo[3 * L + a], mn[a]);
-          atomicMax(&hi[3 * L + a], mx[a]);
+          const U v = Bits<T>::of(so(a)[pq]);
+          ext[a] = v < ext[a] ? v : ext[a];
+          ext[3 + a] = v > ext[3 + a] ? v : ext[3 + a];
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const U mn = wave_min_dpp(ext[a]), mx = wave_max_dpp(ext[3 + a]);
+        if (lane == 0) { lo[a] = mn; hi[a] = mx; }
+      }
+    } else {
+      for (uint32_t q0 = 0; q0 < extent; q0 += 64) {
+        const uint32_t q = q0 + (uint32_t)lane;
+        const uint8_t L = q < extent ? tag(cb)[q] : kNone;
+        const bool part = L != kNone && ((chm >> L) & 1ull);
+        const uint32_t key = part ? (uint32_t)L : 0xFFFFFFFFu;
+        U mn[3], mx[3];
+        if (part) {
+          const uint16_t pq = I(cb)[q];
+          for (int a = 0; a < 3; ++a) mn[a] = mx[a] = Bits<T>::of(so(a)[pq]);
+        } else {
+          for (int a = 0; a < 3; ++a) { mn[a] = Bits<T>::lo_init; mx[a] = 0; }
+        }
+        // segmented min and max of each axis over the chunk (DPP moves, no LDS)
+        const uint32_t prev = dpp_from_prev(key, ~key);
+        U ext[6] = {mn[0], mn[1], mn[2], mx[0], mx[1], mx[2]};
+        const U eid[6] = {Bits<T>::lo_init, Bits<T>::lo_init, Bits<T>::lo_init, 0, 0, 0};
+        seg_scan(ext, prev != key ? 1u : 0u, eid,
+                 [](int k, U a, U b) { return k < 3 ? (a < b ? a : b) : (a > b ? a : b); });
+#pragma unroll
+        for (int a = 0; a < 3; ++a) { mn[a] = ext[a]; mx[a] = ext[3 + a]; }
+        const uint32_t next = dpp_from_next(key, ~key);
+        if (part && (lane == 63 || next != key)) {
+          for (int a = 0; a < 3; ++a) {
+            atomicMin(&lo[3 * L + a], mn[a]);
+            atomicMax(&hi[3 * L + a], mx[a]);
+          }
         }
       }
     }
@@ -300,17 +303,43 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
       for (uint32_t q = (uint32_t)lane; q < extent; q += 64) {
         const uint8_t L = tag(cb)[q];
         if (L == kNone || !((chm >> L) & 1ull)) continue;
-        const uint16_t pq = I(cb)[q];
-        if (packed) {
-          kid[q] = packed_key(so(axis[L])[pq], idr[pq]);
-        } else {
-          kkey[q] = so(axis[L])[pq];
-          kid[q] = sid[pq];
-        }
+        kkey[q] = so(axis[L])[I(cb)[q]];
       }
       wave_lds_sync();
     }
-    // (ii) order each splitting leaf by (coordinate, id); copy the other leaves
+    // (ii) order each splitting leaf by (coordinate, id); copy the other leaves.  Small
+    // paths: by the coordinate, and again with the id ranks if (iii) finds that two pieces
+    // took one slot.
+    for (bool ties = !contig;; ties = true) {
+    if (contig && ties && !ranked) {
+      // id ranks among the cell's pieces (a split superparticle's parts share theirs: they
+      // are never in one leaf), with the ids in registers
+      constexpr int kCh = (S + 63) / 64;
+      uint32_t rk[kCh];
+#pragma unroll 1
+      for (int h = 0; h < kCh; ++h) {
+        const uint32_t q = (uint32_t)(64 * h + lane);
+        const uint64_t iq = q < nstore ? id_of(src[q]) : 0ull;
+        uint32_t r = 0;
+#pragma unroll 1
+        for (uint32_t t0 = 0; t0 < nstore; t0 += 64) {
+          const uint64_t it = t0 + (uint32_t)lane < nstore ? id_of(src[t0 + lane]) : ~0ull;
+          const int te = (int)min(64u, nstore - t0);
+#pragma unroll 1
+          for (int t = 0; t < te; ++t) r += lane_u64(it, t) < iq ? 1u : 0u;
+        }
+#pragma unroll
+        for (int g = 0; g < kCh; ++g) rk[g] = g == h ? r : (h == 0 ? 0u : rk[g]);
+      }
+      wave_lds_sync();
+#pragma unroll
+      for (int h = 0; h < kCh; ++h) {
+        const uint32_t q = (uint32_t)(64 * h + lane);
+        if (q < nstore) src[q] = (uint16_t)rk[h];
+      }
+      ranked = true;
+      wave_lds_sync();
+    }
     for (uint32_t q = (uint32_t)lane; q < extent; q += 64) {
       const uint8_t L = tag(cb)[q];
       if (L == kNone) continue;
@@ -322,34 +351,28 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
         tag(ncb)[RL + (q - Ls)] = (uint8_t)ni;
         continue;
       }
-      const int ax = axis[L];
-      const T kq = so(ax)[pq];
-      const uint64_t iq = packed ? 0ull : sid[pq];
       uint32_t rank = 0;
-      if (packed) {
-        const uint64_t cq = packed_key(kq, idr[pq]);
-        uint32_t r = Ls;
+      if (contig) {
+        const T kq = kkey[q];
         const uint32_t rend = Ls + Ln;
-        for (; r + 4 <= rend; r += 4)
-          rank += (kid[r] < cq ? 1u : 0u) + (kid[r + 1] < cq ? 1u : 0u) + (kid[r + 2] < cq ? 1u : 0u) +
-                  (kid[r + 3] < cq ? 1u : 0u);
-        for (; r < rend; ++r) rank += kid[r] < cq ? 1u : 0u;
-      } else if (contig) {
-        uint32_t r = Ls;
-        const uint32_t rend = Ls + Ln;
-        for (; r + 4 <= rend; r += 4) {
-          const T k0 = kkey[r], k1 = kkey[r + 1], k2 = kkey[r + 2], k3 = kkey[r + 3];
-          const uint64_t i0 = kid[r], i1 = kid[r + 1], i2 = kid[r + 2], i3 = kid[r + 3];
-          rank += (k0 < kq || (k0 == kq && i0 < iq)) ? 1u : 0u;
-          rank += (k1 < kq || (k1 == kq && i1 < iq)) ? 1u : 0u;
-          rank += (k2 < kq || (k2 == kq && i2 < iq)) ? 1u : 0u;
-          rank += (k3 < kq || (k3 == kq && i3 < iq)) ? 1u : 0u;
-        }
-        for (; r < rend; ++r) {
-          const T kr = kkey[r];
-          rank += (kr < kq || (kr == kq && kid[r] < iq)) ? 1u : 0u;
+        if (!ties) {
+          uint32_t r = Ls;
+          for (; r + 4 <= rend; r += 4)
+            rank += (kkey[r] < kq ? 1u : 0u) + (kkey[r + 1] < kq ? 1u : 0u) + (kkey[r + 2] < kq ? 1u : 0u) +
+                    (kkey[r + 3] < kq ? 1u : 0u);
+          for (; r < rend; ++r) rank += kkey[r] < kq ? 1u : 0u;
+        } else {
+          const uint32_t iq = src[pq];
+#pragma unroll 1
+          for (uint32_t r = Ls; r < rend; ++r) {
+            const T kr = kkey[r];
+            rank += (kr < kq || (kr == kq && src[I(cb)[r]] < iq)) ? 1u : 0u;
+          }
         }
       } else {
+        const int ax = axis[L];
+        const T kq = so(ax)[pq];
+        const uint64_t iq = sid[pq];
         for (uint32_t r = Ls; r < Ls + Ln; ++r) {
           const uint16_t pr = I(cb)[r];
           const T kr = so(ax)[pr];
@@ -366,23 +389,25 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
     // lies left of the median if 2x <= W, right of it if 2(x - w) > W, and is the
     // median otherwise; the first two get their child's tag here, the median (and a
     // split superparticle's spare slot) with the children below.
-    uint32_t carry = 0;
+    // The prefix inside a leaf is the wavefront's plain prefix less its value before the
+    // leaf's first slot (both modulo 2^32, their difference exact).
+    uint32_t carry = 0, carry_start = 0;  // total, and prefix before the open leaf, so far
     uint32_t carry_key = 0xFFFFFFFFu;
     bool carry_hit = false;
+    uint32_t placed = 0;
     for (uint32_t q0 = 0; q0 < new_extent; q0 += 64) {
       const uint32_t q = q0 + (uint32_t)lane;
       const uint8_t t8 = q < new_extent ? otag[q] : kNone;
       const bool valid = t8 != kNone;
+      placed += (uint32_t)__popcll(__ballot(valid));
       const uint32_t vkey = valid ? (uint32_t)t8 : 0xFFFFFFFFu;
       const uint32_t w = valid ? sw[I(ncb)[q]] : 0u;
-      // segmented prefix sums of the weights over the chunk (DPP moves, no LDS)
       const uint32_t prev = dpp_from_prev(vkey, ~vkey);
-      uint32_t xs[1] = {w};
-      const uint32_t zid[1] = {0u};
-      const uint32_t seen = seg_scan(xs, prev != vkey ? 1u : 0u, zid,
-                                     [](int, uint32_t a, uint32_t b) { return a + b; });
-      uint32_t x = xs[0];
-      if (!seen && vkey == carry_key) x += carry;
+      const uint32_t P = wave_prefix_dpp(w) + carry, Pe = P - w;
+      const uint32_t first = valid ? (uint32_t)Rg[vkey & 63u] : q;  // the leaf's first slot
+      uint32_t start = __shfl(Pe, first >= q0 ? (int)(first - q0) : 0, 64);
+      if (first < q0) start = carry_start;
+      const uint32_t x = P - start;
       const uint32_t Wv = valid ? LW(cb)[vkey & 63u] : 0u;
       const bool hit = valid && x > Wv - x;  // 2x > W
       const bool up_hit = dpp_from_prev(hit ? 1u : 0u, 0u) != 0u;
@@ -397,9 +422,13 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
         const uint32_t xe = x - w;
         tag(ncb)[q] = !hit ? (uint8_t)ni : (xe > Wv - xe ? (uint8_t)(ni + 1u) : kNone);
       }
-      carry = lane_u32(x, 63);
+      carry = lane_u32(P, 63);
+      carry_start = lane_u32(start, 63);
       carry_key = lane_u32(vkey, 63);
       carry_hit = lane_u32(hit ? 1u : 0u, 63) != 0u;
+    }
+    if (ties || placed == nsplit) break;  // every piece has a slot of its own
+    wave_lds_sync();
     }
     wave_lds_sync();
     // (iv)-(v) children of every splitting leaf, one lane per leaf
@@ -430,7 +459,7 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
     if (lane < nl && chosen) {
       if (super) {
         const uint32_t wm = sw[pm];
-        if (packed) idr[np] = idr[pm];
+        if (contig) src[np] = src[pm];
         else sid[np] = sid[pm];
         for (int a = 0; a < 3; ++a) so(a)[np] = so(a)[pm];
         sw[np] = wm - wl;
