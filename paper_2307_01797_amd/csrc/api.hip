@@ -562,27 +562,27 @@ int itokmc_diagnostics(itokmc_ctx* ctx, itokmc_diag* out) {
   out->n_plus = (int64_t)host[2];
   out->n_minus = (int64_t)host[3];
   out->charge = (int64_t)host[2] - (int64_t)host[1] - (int64_t)host[3];
-  out->outflow_weight = c.outflow;
-  for (int r = 0; r < 5; ++r) out->fires[r] = c.fires[r];
-  out->photons_emitted = c.ph_emitted;
-  out->photons_absorbed = c.ph_absorbed;
-  out->photons_lost = c.ph_lost;
-  out->created = c.created;
-  out->removed_weight = c.removed;
-  out->merged_cells = c.merged;
+  out->outflow_weight = c.total(T_OUTFLOW);
+  for (int r = 0; r < 5; ++r) out->fires[r] = c.total(T_FIRES + r);
+  out->photons_emitted = c.total(T_EMITTED);
+  out->photons_absorbed = c.total(T_ABSORBED);
+  out->photons_lost = c.total(T_LOST);
+  out->created = c.total(T_CREATED);
+  out->removed_weight = c.total(T_REMOVED);
+  out->merged_cells = c.total(T_MERGED);
   out->step = ctx->step;
   out->solver_cycles = ctx->last_cycles;
   out->solver_relres = ctx->last_relres;
   out->rho_sum = 1.602176634e-19 * (double)out->charge;
   out->overflow = c.overflow;
-  out->particle_steps = c.pushed;
+  out->particle_steps = c.total(T_PUSHED);
   out->merge_skipped = c.merge_skipped;
   out->occupied_cells = c.n_occ;
   out->queued_cells = c.n_work;
   out->wave_cells = c.n_cfull + c.n_cmerge;
-  out->ion_outflow_plus = c.ion_out[0];
-  out->ion_outflow_minus = c.ion_out[1];
-  out->couple_pieces = c.couple_pieces;
+  out->ion_outflow_plus = c.total(T_ION_OUT);
+  out->ion_outflow_minus = c.total(T_ION_OUT + 1);
+  out->couple_pieces = c.total(T_PIECES);
   out->solver_cycles_total = ctx->total_cycles;
   out->solves_total = ctx->total_solves;
   if (c.overflow) return set_error(ctx, ITOKMC_ECAPACITY, "capacity exceeded (flags %u)", c.overflow);

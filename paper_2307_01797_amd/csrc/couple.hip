@@ -90,8 +90,8 @@ __global__ void __launch_bounds__(256) k_couple_light(Bank b, Counters* ctr, Ste
   created = wave_sum64(created);
   removed = wave_sum64(removed);
   if (lane_id() == 0) {
-    if (created) atomicAdd(&ctr->created, (unsigned long long)created);
-    if (removed) atomicAdd(&ctr->removed, (unsigned long long)removed);
+    tally_add(ctr, T_CREATED, created);
+    tally_add(ctr, T_REMOVED, removed);
   }
 }
 
@@ -143,10 +143,10 @@ __global__ void __launch_bounds__(64, 5) k_couple(Bank b, Counters* ctr, int whi
     if (mine && r != 1 && q < K.cap) write_product<T>(b, q, c, c, (uint32_t)lane, wb, wr, K.step, K.key);
   }
   if (lane == 0) {
-    if (created) atomicAdd(&ctr->created, (unsigned long long)created);
-    if (removed) atomicAdd(&ctr->removed, (unsigned long long)removed);
-    if (merged) atomicAdd(&ctr->merged, (unsigned long long)merged);
-    if (pieces) atomicAdd(&ctr->couple_pieces, (unsigned long long)pieces);
+    tally_add(ctr, T_CREATED, created);
+    tally_add(ctr, T_REMOVED, removed);
+    tally_add(ctr, T_MERGED, merged);
+    tally_add(ctr, T_PIECES, pieces);
   }
 }
 
@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(64) k_merge_tier(Bank b, Counters* ctr, int wh
       }
     }
   }
-  if (lane_id() == 0 && merged) atomicAdd(&ctr->merged, (unsigned long long)merged);
+  if (lane_id() == 0) tally_add(ctr, T_MERGED, merged);
 }
 
 }  // namespace

@@ -742,8 +742,8 @@ __global__ void __launch_bounds__(256) k_push_field(Bank a, Counters* ctr, int w
   out_w = wave_sum64(out_w);
   pushed = wave_sum64(pushed);
   if (lane_id() == 0) {
-    if (out_w) atomicAdd(&ctr->outflow, (unsigned long long)out_w);
-    if (pushed) atomicAdd(&ctr->pushed, (unsigned long long)pushed);
+    tally_add(ctr, T_OUTFLOW, out_w);
+    tally_add(ctr, T_PUSHED, pushed);
   }
 }
 

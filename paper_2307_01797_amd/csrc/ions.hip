@@ -160,8 +160,8 @@ __global__ void __launch_bounds__(256) k_ion_move(StepConst K, const T* E4, IonM
   }
   const uint64_t op = wave_sum64(out[0]), om = wave_sum64(out[1]);
   if (lane_id() == 0) {
-    if (op) atomicAdd(&ctr->ion_out[0], (unsigned long long)op);
-    if (om) atomicAdd(&ctr->ion_out[1], (unsigned long long)om);
+    tally_add(ctr, T_ION_OUT, op);
+    tally_add(ctr, T_ION_OUT + 1, om);
   }
 }
 
@@ -197,8 +197,8 @@ __global__ void __launch_bounds__(256) k_ion_big(StepConst K, const T* E4, IonMo
   }
   const uint64_t op = wave_sum64(out[0]), om = wave_sum64(out[1]);
   if (lane_id() == 0) {
-    if (op) atomicAdd(&ctr->ion_out[0], (unsigned long long)op);
-    if (om) atomicAdd(&ctr->ion_out[1], (unsigned long long)om);
+    tally_add(ctr, T_ION_OUT, op);
+    tally_add(ctr, T_ION_OUT + 1, om);
   }
 }
 

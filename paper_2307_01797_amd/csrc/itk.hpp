@@ -31,34 +31,63 @@ struct Bank {
   uint32_t* rank;  // position inside the destination cell, written by the push
 };
 
-// Device-resident counters and tallies (one 256-byte block of the arena).
-struct Counters {
-  uint32_t n[2];          // particles per bank (including dead slots, w == 0)
-  uint32_t overflow;      // ITOKMC_OVF_*: bit 0 particle capacity, bit 1 a cell too
-                          // large for every merge staging (left unmerged)
-  uint32_t n_occ;         // occupied cells after binning
-  uint32_t n_work;        // cells needing coupling / merge
-  uint32_t sorted;        // particles placed by the last counting sort
-  uint32_t n_heavy;       // occupied cells left to the full KMC pass
-  uint32_t n_huge;        // cells deferred past the mid-size merge staging
-  unsigned long long outflow, created, removed, merged;
-  unsigned long long fires[5];  // ionization, attachment, emission, e-ion, ion-ion
-  unsigned long long ph_emitted, ph_absorbed, ph_lost;
-  unsigned long long pushed;   // live particles advanced by the transport kernels
-  uint32_t merge_skipped;      // cells too large for the LDS merge (left unmerged)
-  uint32_t n_big;              // cells deferred to the mid-size merge staging
-  uint32_t n_cfull;            // cells for the wavefront coupling pass (everything)
-  uint32_t n_cmerge;           // cells for the wavefront coupling pass (merge only)
-  unsigned long long couple_pieces;  // particles gathered by the wavefront coupling pass
+// Atomics on one 128-byte line are a serial chain of about 12 ns each (measured), so
+// counters that many workgroups append to have lines of their own, and the tallies, which
+// every wavefront of a kernel adds to and which only the host reads (the push count also
+// the stop rule), are spread over kTallyLines lines by workgroup: a kernel of 32768
+// wavefronts with three tallies took 1.2 ms for them alone.
+struct PaddedPair {
+  uint32_t w[64];
+  __host__ __device__ uint32_t& operator[](int i) { return w[32 * i]; }
+  __host__ __device__ const uint32_t& operator[](int i) const { return w[32 * i]; }
+};
+enum Tally { T_OUTFLOW = 0, T_CREATED, T_REMOVED, T_MERGED,
+             T_FIRES,      // five: ionization, attachment, emission, e-ion, ion-ion
+             T_EMITTED = T_FIRES + 5, T_ABSORBED, T_LOST,
+             T_PUSHED,     // live particles advanced by the transport kernels
+             T_PIECES,     // particles gathered by the wavefront coupling pass
+             T_ION_OUT,    // two: positive and negative ions lost through domain faces
+             T_NUM = T_ION_OUT + 2 };
+constexpr int kTallyLines = 64;
+struct alignas(128) TallyLine {
+  unsigned long long v[16];
+};
+static_assert(T_NUM <= 16, "a tally line is 128 bytes");
+
+// Device-resident counters and tallies.
+struct alignas(128) Counters {
+  PaddedPair n;                        // particles per bank (including dead slots, w == 0)
+  alignas(128) uint32_t n_work;        // cells needing coupling / merge
+  alignas(128) uint32_t n_heavy;       // occupied cells left to the full KMC pass
+  alignas(128) uint32_t n_cfull;       // cells for the wavefront coupling pass (everything)
+  alignas(128) uint32_t n_cmerge;      // cells for the wavefront coupling pass (merge only)
+  alignas(128) uint32_t n_big;         // cells deferred to the mid-size merge staging
+  alignas(128) uint32_t n_huge;        // cells deferred past the mid-size merge staging
+  alignas(128) uint32_t n_ionbig;      // ion species of large total mean left to the second pass
+  alignas(128) uint32_t overflow;      // ITOKMC_OVF_*: bit 0 particle capacity, bit 1 a cell too
+                                       // large for every merge staging (left unmerged)
+  uint32_t n_occ;                      // occupied cells after binning
+  uint32_t sorted;                     // particles placed by the last counting sort
+  uint32_t merge_skipped;              // cells too large for the LDS merge (left unmerged)
   // device-side stop rule (itokmc_step_until): once halt is set, every kernel of the
   // step path returns at entry, so the state stays that of the last step taken
   uint32_t halt;
   uint32_t steps_done;
-  unsigned long long pushed_mark;    // `pushed` at the start of the current step
-  unsigned long long ion_out[2];     // positive and negative ions lost through domain faces
-  uint32_t n_ionbig;                 // ion species of large total mean left to the second pass
-  uint32_t pad_ion;
+  unsigned long long pushed_mark;      // T_PUSHED at the start of the current step
+  TallyLine tally[kTallyLines];
+
+  // Host copy: a tally's total.
+  unsigned long long total(int t) const {
+    unsigned long long s = 0;
+    for (int i = 0; i < kTallyLines; ++i) s += tally[i].v[t];
+    return s;
+  }
 };
+
+// Add a wavefront's sum to a tally (one lane calls).
+__device__ __forceinline__ void tally_add(Counters* ctr, int t, unsigned long long v) {
+  if (v) atomicAdd(&ctr->tally[blockIdx.x & (kTallyLines - 1)].v[t], v);
+}
 
 // Device-side copy of the per-step constants shared by the kernels.
 struct StepConst {

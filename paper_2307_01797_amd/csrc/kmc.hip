@@ -170,12 +170,10 @@ __global__ void __launch_bounds__(kFast ? 256 : 64) k_kmc_step(
   }
   t0 = wave_sum64(t0); t1 = wave_sum64(t1); t2 = wave_sum64(t2);
   if (lane_id() == 0) {
-    if (t0) atomicAdd(&ctr->fires[0], (unsigned long long)t0);
-    if (t1) atomicAdd(&ctr->fires[1], (unsigned long long)t1);
-    if (t2) {
-      atomicAdd(&ctr->fires[2], (unsigned long long)t2);
-      atomicAdd(&ctr->ph_emitted, (unsigned long long)t2);
-    }
+    tally_add(ctr, T_FIRES, t0);
+    tally_add(ctr, T_FIRES + 1, t1);
+    tally_add(ctr, T_FIRES + 2, t2);
+    tally_add(ctr, T_EMITTED, t2);
   }
 }
 
@@ -230,9 +228,8 @@ __global__ void __launch_bounds__(64) k_kmc_step_rec(
   }
   for (int r = 0; r < 5; ++r) t[r] = wave_sum64(t[r]);
   if (lane_id() == 0) {
-    for (int r = 0; r < 5; ++r)
-      if (t[r]) atomicAdd(&ctr->fires[r], (unsigned long long)t[r]);
-    if (t[2]) atomicAdd(&ctr->ph_emitted, (unsigned long long)t[2]);
+    for (int r = 0; r < 5; ++r) tally_add(ctr, T_FIRES + r, t[r]);
+    tally_add(ctr, T_EMITTED, t[2]);
   }
 }
 
@@ -265,7 +262,7 @@ __global__ void __launch_bounds__(256) k_kmc_ions(KmcParams P, StepConst K, Coun
     t4 += (uint64_t)f[4];
   }
   t4 = wave_sum64(t4);
-  if (lane_id() == 0 && t4) atomicAdd(&ctr->fires[4], (unsigned long long)t4);
+  if (lane_id() == 0) tally_add(ctr, T_FIRES + 4, t4);
 }
 
 // Independent cells (unit parity): the three-reaction code when both recombination
@@ -397,16 +394,25 @@ __global__ void __launch_bounds__(64, 2) k_kmc_run(KmcParams P, uint32_t seed, u
 
 // Device-side stop rule of a run (itokmc_step_until): a run stops after the first step
 // that began with at least stop_particles live particles (the push counts them).
-__global__ void k_stop_begin(Counters* ctr) {
+static_assert(kTallyLines == 64, "one lane per tally line");
+__device__ __forceinline__ unsigned long long pushed_total(const Counters* ctr) {
+  return wave_sum64(ctr->tally[lane_id()].v[T_PUSHED]);
+}
+// One wavefront each.
+__global__ void __launch_bounds__(64) k_stop_begin(Counters* ctr) {
+  const unsigned long long pushed = pushed_total(ctr);
+  if (lane_id()) return;
   ctr->halt = 0u;
   ctr->steps_done = 0u;
-  ctr->pushed_mark = ctr->pushed;
+  ctr->pushed_mark = pushed;
 }
-__global__ void k_stop_step(Counters* ctr, uint64_t stop_particles) {
+__global__ void __launch_bounds__(64) k_stop_step(Counters* ctr, uint64_t stop_particles) {
   if (ctr->halt) return;
+  const unsigned long long pushed = pushed_total(ctr);
+  if (lane_id()) return;
   ctr->steps_done += 1u;
-  const unsigned long long live = ctr->pushed - ctr->pushed_mark;
-  ctr->pushed_mark = ctr->pushed;
+  const unsigned long long live = pushed - ctr->pushed_mark;
+  ctr->pushed_mark = pushed;
   if (stop_particles && live >= stop_particles) ctr->halt = 1u;
 }
 __global__ void k_stop_end(Counters* ctr) { ctr->halt = 0u; }
@@ -452,11 +458,11 @@ hipError_t launch_kmc_step(itokmc_ctx* ctx, const StepConst& k, const FieldRates
 }
 
 hipError_t launch_stop_begin(itokmc_ctx* ctx) {
-  k_stop_begin<<<1, 1, 0, ctx->s>>>(ctx->ctr);
+  k_stop_begin<<<1, 64, 0, ctx->s>>>(ctx->ctr);
   return hipGetLastError();
 }
 hipError_t launch_stop_step(itokmc_ctx* ctx, uint64_t stop_particles) {
-  k_stop_step<<<1, 1, 0, ctx->s>>>(ctx->ctr, stop_particles);
+  k_stop_step<<<1, 64, 0, ctx->s>>>(ctx->ctr, stop_particles);
   return hipGetLastError();
 }
 hipError_t launch_stop_end(itokmc_ctx* ctx) {

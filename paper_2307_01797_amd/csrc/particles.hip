@@ -203,8 +203,8 @@ __global__ void __launch_bounds__(kBlock) k_push_uniform(Bank a, Counters* ctr, 
   out_w = wave_sum64(out_w);
   pushed = wave_sum64(pushed);
   if (lane_id() == 0) {
-    if (out_w) atomicAdd(&ctr->outflow, (unsigned long long)out_w);
-    if (pushed) atomicAdd(&ctr->pushed, (unsigned long long)pushed);
+    tally_add(ctr, T_OUTFLOW, out_w);
+    tally_add(ctr, T_PUSHED, pushed);
   }
 }
 
@@ -318,8 +318,8 @@ __global__ void __launch_bounds__(kBlock) k_photons(Bank a, Counters* ctr, int w
   absorbed = wave_sum64(absorbed);
   lost = wave_sum64(lost);
   if (lane_id() == 0) {
-    if (absorbed) atomicAdd(&ctr->ph_absorbed, (unsigned long long)absorbed);
-    if (lost) atomicAdd(&ctr->ph_lost, (unsigned long long)lost);
+    tally_add(ctr, T_ABSORBED, absorbed);
+    tally_add(ctr, T_LOST, lost);
   }
 }
 
