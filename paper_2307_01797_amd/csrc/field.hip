@@ -360,65 +360,88 @@ template <> struct NormalsF<float> {
 template <typename T> struct DepAcc;
 template <> struct DepAcc<double> {
   using S = double;
-  __device__ static S enc0(double a) { return a; }
-  __device__ static S enc1(double a) { return a; }
+  static constexpr double kUnit[2] = {1.0, 1.0};
+  __device__ static S enc(double a, bool) { return a; }
   __device__ static double dec0(S v) { return v; }
   __device__ static double dec1(S v) { return v; }
 };
 template <> struct DepAcc<float> {
   using S = unsigned long long;
-  __device__ static S enc0(double a) { return (S)rint(a * 0x1p32); }
-  __device__ static S enc1(double a) { return (S)rint(a * 0x1p28); }
+  static constexpr double kUnit[2] = {0x1p32, 0x1p28};  // units per (mu w) and per electron
+  // a in units (the scaling by a power of two is exact, so it is applied to the particle's
+  // weight once), rounded to the nearest integer.  fits: a < 2^52, where adding 2^52 leaves
+  // that integer in the mantissa (one addition and a mask instead of the conversion).
+  __device__ static S enc(double a, bool fits) {
+    if (fits) return (S)__double_as_longlong(a + 0x1p52) & 0xFFFFFFFFFFFFFull;
+    return (S)rint(a);
+  }
   __device__ static double dec0(S v) { return (double)v * 0x1p-32; }
   __device__ static double dec1(S v) { return (double)v * 0x1p-28; }
 };
 
-// Charge deposit for the field solve.  A workgroup takes a chunk of kDepChunk
-// consecutive (cell-sorted, hence spatially compact) particles and accumulates their
-// 8-node CIC contributions in an LDS hash table keyed by grid node (linear probing,
-// at most kDepProbes probes, then a direct global atomic); the table is flushed with
-// one global atomic per touched node and field.  Mode 0 deposits the electron number
-// at X^k only (initial field); mode 1 deposits the conductivity weight mu(|E^k|) w at
-// X^k and the electron number at X_dagger (the position after the diffusive part of
-// the step, with the normals of the push), and keeps each particle's mobility mu^k for
-// the push, which then reads it instead of interpolating E^k again.
-// A 1024-entry table per 256-particle chunk, one particle per thread (20 KB of LDS):
-// small tables raise the number of resident workgroups, a table four times the chunk
-// keeps probing short, and with the row-ordered slots a chunk's nodes rarely collide.
+// Charge deposit for the field solve.  Mode 0 deposits the electron number at X^k only
+// (initial field); mode 1 deposits the conductivity weight mu(|E^k|) w at X^k and the
+// electron number at X_dagger (the position after the diffusive part of the step, with the
+// normals of the push), and keeps each particle's mobility mu^k for the push, which then
+// reads it instead of interpolating E^k again.
+//
+// A workgroup takes a chunk of kDepChunk consecutive (cell-sorted, hence spatially compact)
+// particles, one per thread, and sums in LDS on two levels.
+//
+// * Cell blocks: each run of equal cells in a wavefront, kDepRuns of them at a time, has
+//   the nodes around its cell as a small dense array (CIC and the conductivity 3^3; TSC's
+//   displaced charge 5^3), so that a contribution is one LDS atomic at a fixed offset,
+//   without a node index, a hash or a key, and neighbouring lanes of a run take its nodes
+//   in different orders: 64 lanes that add to one address take 128 cycles, to 8 of them in
+//   turn 15.
+// * Table: the blocks of a wavefront of at most kDepDense runs (cells of 8 particles and
+//   more) are added, one node per lane, to a hash table keyed by grid node (linear probing,
+//   at most kDepProbes probes, then a direct global atomic), flushed with one global atomic
+//   per touched node and field: consecutive cells share most of their nodes.  The blocks of
+//   a wavefront of more runs would fill the table with nodes that hardly repeat, so they go
+//   to the grid directly, a node per lane: a row of a block is one request of the global
+//   atomics (25e9 lines of 64 B a second, whatever they hold), where a particle by itself
+//   is one request per node.
+// * A particle displaced out of its block adds to the table by itself.
+//
+// A block stays worth its zeroing and its flush down to single particles, so every
+// wavefront takes this way; the table takes the blocks of at most kDepDense runs (of 2 or
+// 64 instead of 8: 2.92 and 3.25 ms where 8 takes 1.88, 4.5e7 particles).  CIC in single
+// precision: 512 entries (24 KB with the blocks) and 79 VGPRs let six workgroups of a CU
+// overlap their loads; 1024 entries leave four (2.37 ms).  What bounds it is that latency:
+// the loads, the field gather and the flush of a chunk follow each other.  Before, each
+// lane added its own contributions to a table of 1024 entries (TSC: sums over runs by
+// segmented scans first): CIC 2.15 ms at 4.5e7 particles, 0.40 -> 0.37 ms at 6.3e6; TSC
+// 1.45 -> 0.74 ms at 3.7e6 (the same table, overfull with the nodes of single particles,
+// and 2.5e7 -> 1.3e7 global requests at the end of a run).  Double precision 0.10 ms at
+// 4e5 particles either way.
 constexpr int kDepChunk = 256;
 constexpr int kDepProbes = 8;
+template <int SH> constexpr int kDepRuns = SH == 0 ? 8 : 4;  // 4: 2.01 ms, 16: 2.21 (CIC)
+constexpr int kDepDense = 8;
 constexpr uint32_t kEmptyKey = 0xFFFFFFFFu;
-template <typename T> struct DepTbl { static constexpr int log2n = 10; };
-
-template <typename T, int L2>
-__device__ __forceinline__ void tbl_add(uint32_t* keys, typename DepAcc<T>::S* v0,
-                                        typename DepAcc<T>::S* v1, uint32_t node, uint32_t h, double a,
-                                        double b, typename DepAcc<T>::S* g0, typename DepAcc<T>::S* g1) {
-  using A = DepAcc<T>;
-  constexpr uint32_t mask = (1u << L2) - 1u;
-  for (int probe = 0; probe < kDepProbes; ++probe) {
-    uint32_t k = keys[h];
-    if (k == kEmptyKey) {
-      const uint32_t prev = atomicCAS(&keys[h], kEmptyKey, node);
-      k = prev == kEmptyKey ? node : prev;
-    }
-    if (k == node) {
-      if (a != 0.0) atomicAdd(&v0[h], A::enc0(a));
-      if (b != 0.0) atomicAdd(&v1[h], A::enc1(b));
-      return;
-    }
-    h = (h + 1u) & mask;
-  }
-  if (a != 0.0) atomicAdd(&g0[node], A::enc0(a));
-  if (b != 0.0) atomicAdd(&g1[node], A::enc1(b));
+template <typename T, int SH> constexpr int kDepL2 = SH == 0 && sizeof(T) == 4 ? 9 : 10;
+// Nodes per axis of a run's block of the displaced charge.
+template <int SH> constexpr int kDepW = SH == 0 ? 3 : 5;
+template <int SH> constexpr int kDepBlock = 27 + kDepW<SH> * kDepW<SH> * kDepW<SH>;
+template <typename T, int SH>
+constexpr size_t dep_lds_bytes() {
+  return ((size_t)1 << kDepL2<T, SH>) * (4 + 2 * sizeof(typename DepAcc<T>::S)) +
+         (size_t)(kDepChunk / 64) * kDepRuns<SH> * kDepBlock<SH> * sizeof(typename DepAcc<T>::S);
 }
 
-// tbl_add for one field and an already encoded (fixed-point) value.
-template <int F, int L2>
-__device__ __forceinline__ void tbl_add_enc(uint32_t* keys, unsigned long long* v,
-                                            uint32_t node, uint32_t h, unsigned long long e,
-                                            unsigned long long* g) {
-  constexpr uint32_t mask = (1u << L2) - 1u;
+// Slot of a node in the table: the row hashed, x kept in order, so that a row's nodes sit
+// in consecutive slots and the flush's atomics of neighbouring lanes share lines.
+template <int L2>
+__device__ __forceinline__ uint32_t tbl_slot(uint32_t x, uint32_t row) {
+  return (x + ((row * 2654435761u) >> (32 - L2))) & ((1u << L2) - 1u);
+}
+
+// Add e to the node's sum of one field (v in the table, g in global memory).
+template <typename S, int L2>
+__device__ __forceinline__ void tbl_put(uint32_t* keys, S* v, uint32_t node, uint32_t h, S e, S* g) {
+  if (e == (S)0) return;
+#pragma unroll 1
   for (int probe = 0; probe < kDepProbes; ++probe) {
     uint32_t k = keys[h];
     if (k == kEmptyKey) {
@@ -429,232 +452,257 @@ __device__ __forceinline__ void tbl_add_enc(uint32_t* keys, unsigned long long* 
       atomicAdd(&v[h], e);
       return;
     }
-    h = (h + 1u) & mask;
+    h = (h + 1u) & ((1u << L2) - 1u);
   }
   atomicAdd(&g[node], e);
 }
 
+// A particle's tent weights along the three axes and their node offsets (0 or 1), in the
+// lane's own order: lane l starts at corner l mod 8, so that the lanes of a run, which add
+// to the same nodes, do not add to one node at the same time.
+template <typename T>
+struct Corner {
+  T w[3][2];
+  int o[3][2];
+};
+template <typename T>
+__device__ __forceinline__ Corner<T> corners(int lane, T fx, T fy, T fz) {
+  Corner<T> c;
+  const T f[3] = {fx, fy, fz};
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const int flip = (lane >> q) & 1;
+    const T g = (T)1 - f[q];
+    c.w[q][0] = flip ? f[q] : g;
+    c.w[q][1] = flip ? g : f[q];
+    c.o[q][0] = flip;
+    c.o[q][1] = 1 - flip;
+  }
+  return c;
+}
+
+// The 8 CIC contributions q wt of one particle to the table (q in units; fits: as enc).
 template <typename T, int L2>
-__device__ __forceinline__ void tbl_cic(uint32_t* keys, typename DepAcc<T>::S* v0,
-                                        typename DepAcc<T>::S* v1, const StepConst& K, int i0,
-                                        int j0, int k0, T fx, T fy, T fz, double qa, double qb,
-                                        typename DepAcc<T>::S* g0, typename DepAcc<T>::S* g1) {
+__device__ __forceinline__ void tbl_cic(uint32_t* keys, typename DepAcc<T>::S* v, const StepConst& K, int i0,
+                                        int j0, int k0, const Corner<T>& c, double q, bool fits,
+                                        typename DepAcc<T>::S* g) {
+  using S = typename DepAcc<T>::S;
 #pragma unroll
   for (int cc = 0; cc < 8; ++cc) {
     const int di = cc & 1, dj = (cc >> 1) & 1, dk = (cc >> 2) & 1;
-    const T wt = (di ? fx : (T)1 - fx) * (dj ? fy : (T)1 - fy) * (dk ? fz : (T)1 - fz);
-    const int ii = i0 + di, jj = j0 + dj, kk = k0 + dk;
+    const T wt = c.w[0][di] * c.w[1][dj] * c.w[2][dk];
+    const int ii = i0 + c.o[0][di], jj = j0 + c.o[1][dj], kk = k0 + c.o[2][dk];
     if (wt == (T)0 || ii >= K.nx || jj >= K.ny || kk >= K.nz) continue;
     const uint32_t row = (uint32_t)jj + (uint32_t)K.ny * (uint32_t)kk;
-    const uint32_t node = (uint32_t)ii + (uint32_t)K.nx * row;
-    // table slot: the row hashed, x kept in order, so that a row's nodes sit in
-    // consecutive slots and the flush's atomics of neighbouring lanes share lines
-    const uint32_t h = ((uint32_t)ii + ((row * 2654435761u) >> (32 - L2))) & ((1u << L2) - 1u);
-    tbl_add<T, L2>(keys, v0, v1, node, h, qa * (double)wt, qb * (double)wt, g0, g1);
+    tbl_put<S, L2>(keys, v, (uint32_t)ii + (uint32_t)K.nx * row, tbl_slot<L2>((uint32_t)ii, row),
+                   DepAcc<T>::enc(q * (double)wt, fits), g);
   }
 }
 
-// The 27 TSC contributions of one particle into the table (clamped wall nodes repeat
-// and simply add), with the same slot rule.
+// The 27 TSC contributions of one particle (clamped wall nodes repeat and simply add).
 template <typename T, int L2>
-__device__ __forceinline__ void tbl_tsc(uint32_t* keys, typename DepAcc<T>::S* v0,
-                                        typename DepAcc<T>::S* v1, const StepConst& K, const Tsc<T>& s,
-                                        double qa, double qb, typename DepAcc<T>::S* g0,
-                                        typename DepAcc<T>::S* g1) {
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      const uint32_t row = (uint32_t)s.iy[b] + (uint32_t)K.ny * (uint32_t)s.iz[c];
-      const uint32_t hr = (row * 2654435761u) >> (32 - L2);
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const T wt = (s.wx[a] * s.wy[b]) * s.wz[c];
-        if (wt == (T)0) continue;
-        const uint32_t node = (uint32_t)s.ix[a] + (uint32_t)K.nx * row;
-        const uint32_t h = ((uint32_t)s.ix[a] + hr) & ((1u << L2) - 1u);
-        tbl_add<T, L2>(keys, v0, v1, node, h, qa * (double)wt, qb * (double)wt, g0, g1);
-      }
-    }
-  }
-}
-
-// Single precision, TSC shape, one particle per lane (all lanes present; inactive lanes
-// contribute nothing).  The lanes of a wavefront hold consecutive, cell-sorted
-// particles, and the 27 nodes of a particle depend only on its cell indices j (before
-// wall clamping) along the three axes, so the lanes of a run of equal j share them.
-// Each node's fixed-point contributions (exact integers: their sum does not depend on
-// the order) are summed over every run with a segmented scan, and only the run's last
-// lane inserts the sum: a third of the table atomics when cells hold three particles.
-// F: 0 conductivity (enc0, v0/g0), 1 electron number (enc1, v1/g1).
-template <int F, int L2>
-__device__ __forceinline__ void tbl_tsc_runs(uint32_t* keys, unsigned long long* v0,
-                                             unsigned long long* v1, const StepConst& K,
-                                             const Tsc<float>& s, bool active, int jx, int jy,
-                                             int jz, double q, unsigned long long* g0,
-                                             unsigned long long* g1) {
-  using A = DepAcc<float>;
-  const int lane = lane_id();
-  // run key: the three cell indices, each biased into 21 bits (an index off the grid by
-  // up to 2^20 cells still has a key of its own); inactive lanes all differ from it
-  const uint64_t key = active ? ((uint64_t)(uint32_t)(jx + (1 << 20)) << 42) |
-                                    ((uint64_t)(uint32_t)(jy + (1 << 20)) << 21) |
-                                    (uint64_t)(uint32_t)(jz + (1 << 20))
-                              : ~0ull;
-  const uint32_t klo = (uint32_t)key, khi = (uint32_t)(key >> 32);
-  const uint32_t plo = dpp_from_prev(klo, ~klo), phi = dpp_from_prev(khi, ~khi);
-  const uint32_t nlo = dpp_from_next(klo, ~klo), nhi = dpp_from_next(khi, ~khi);
-  const uint32_t head = (plo != klo || phi != khi) ? 1u : 0u;
-  const bool tail = active && (lane == 63 || nlo != klo || nhi != khi);
-  // no run of two or more in the wavefront (sparse cells): every lane inserts its own
-  // contributions, as without the run sums, and the scans are skipped
-  const bool runs = __ballot(active && lane > 0 && head == 0u) != 0ull;
-  const uint64_t zid[1] = {0ull};
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      const uint32_t row = (uint32_t)s.iy[b] + (uint32_t)K.ny * (uint32_t)s.iz[c];
-      const uint32_t hr = (row * 2654435761u) >> (32 - L2);
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const float wt = (s.wx[a] * s.wy[b]) * s.wz[c];
-        const double x = q * (double)wt;
-        uint64_t v[1] = {active && x != 0.0 ? (F == 0 ? A::enc0(x) : A::enc1(x)) : 0ull};
-        if (runs) (void)seg_scan(v, head, zid, [](int, uint64_t u, uint64_t w) { return u + w; });
-        if (tail && v[0] != 0ull) {
-          const uint32_t node = (uint32_t)s.ix[a] + (uint32_t)K.nx * row;
-          const uint32_t h = ((uint32_t)s.ix[a] + hr) & ((1u << L2) - 1u);
-          tbl_add_enc<F, L2>(keys, F == 0 ? v0 : v1, node, h, v[0], F == 0 ? g0 : g1);
-        }
-      }
-    }
-  }
-}
-
-// Single precision: at least 7 waves per SIMD (72 VGPRs, no spills), which measured about
-// 3% faster than the compiler's 75 VGPRs and 6 waves in a side-by-side run on the same
-// state; 8 waves spill and are slower.  Double precision keeps the compiler's choice (a
-// 72-VGPR bound spills).
-// The TSC form (SH = 1: 27 nodes per deposit and gather) keeps the compiler's choice.
-template <typename T> constexpr int kDepMinWaves = sizeof(T) == 4 ? 7 : 1;
-template <typename T, int L2, int SH>
-__global__ void __launch_bounds__(256, SH == 0 ? kDepMinWaves<T> : 1) k_field_deposit_lds(Bank a, const Counters* ctr, int which,
-                                                          StepConst K, const void* E4, Coef co,
-                                                          int mode, typename DepAcc<T>::S* sig,
-                                                          typename DepAcc<T>::S* ne, uint32_t chunk,
-                                                          T* mu_out) {
+__device__ __forceinline__ void tbl_tsc(uint32_t* keys, typename DepAcc<T>::S* v, const StepConst& K,
+                                        const Tsc<T>& s, double q, bool fits, typename DepAcc<T>::S* g) {
   using S = typename DepAcc<T>::S;
-  constexpr int TBL = 1 << L2;
+#pragma unroll 1
+  for (int cb = 0; cb < 9; ++cb) {
+    const int c = cb / 3, b = cb - 3 * c;
+    const T wy = b == 0 ? s.wy[0] : b == 1 ? s.wy[1] : s.wy[2], wz = c == 0 ? s.wz[0] : c == 1 ? s.wz[1] : s.wz[2];
+    const int iy = b == 0 ? s.iy[0] : b == 1 ? s.iy[1] : s.iy[2], iz = c == 0 ? s.iz[0] : c == 1 ? s.iz[1] : s.iz[2];
+    const uint32_t row = (uint32_t)iy + (uint32_t)K.ny * (uint32_t)iz;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const T wt = (s.wx[a] * wy) * wz;
+      tbl_put<S, L2>(keys, v, (uint32_t)s.ix[a] + (uint32_t)K.nx * row, tbl_slot<L2>((uint32_t)s.ix[a], row),
+                     DepAcc<T>::enc(q * (double)wt, fits), g);
+    }
+  }
+}
+
+// The same contributions to a run's block (W nodes per axis): blk points at the particle's
+// lowest node.  TSC: lane l starts at node l mod 27 (rotated along each axis).
+template <typename T, int W>
+__device__ __forceinline__ void blk_cic(typename DepAcc<T>::S* blk, const Corner<T>& c, double q, bool fits) {
+#pragma unroll
+  for (int cc = 0; cc < 8; ++cc) {
+    const int di = cc & 1, dj = (cc >> 1) & 1, dk = (cc >> 2) & 1;
+    const T wt = c.w[0][di] * c.w[1][dj] * c.w[2][dk];
+    atomicAdd(&blk[c.o[0][di] + W * (c.o[1][dj] + W * c.o[2][dk])], DepAcc<T>::enc(q * (double)wt, fits));
+  }
+}
+template <typename T>
+__device__ __forceinline__ void rot3(int r, int stride, const T w[3], T v[3], int o[3]) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    v[q] = r == 0 ? w[q] : r == 1 ? w[(q + 1) % 3] : w[(q + 2) % 3];
+    o[q] = stride * (r == 0 ? q : r == 1 ? (q + 1) % 3 : (q + 2) % 3);
+  }
+}
+template <typename T>
+__device__ __forceinline__ void blk_tsc(typename DepAcc<T>::S* blk, int W, int lane, const Tsc<T>& s, double q,
+                                        bool fits) {
+  T wx[3], wy[3], wz[3];
+  int ox[3], oy[3], oz[3];
+  rot3<T>(lane % 3, 1, s.wx, wx, ox);
+  rot3<T>(lane / 3 % 3, W, s.wy, wy, oy);
+  rot3<T>(lane / 9 % 3, W * W, s.wz, wz, oz);
+#pragma unroll
+  for (int c = 0; c < 3; ++c)
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const T wt = (wx[a] * wy[b]) * wz[c];
+        atomicAdd(&blk[ox[a] + (oy[b] + oz[c])], DepAcc<T>::enc(q * (double)wt, fits));
+      }
+}
+
+template <typename T, int SH>
+__global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? 6 : 4) : (SH == 0 ? 4 : 1))
+    k_field_deposit_lds(Bank a, const Counters* ctr, int which, StepConst K, const void* E4, Coef co, int mode,
+                        typename DepAcc<T>::S* sig, typename DepAcc<T>::S* ne, T* mu_out) {
+  using A = DepAcc<T>;
+  using S = typename A::S;
+  constexpr int L2 = kDepL2<T, SH>, TBL = 1 << L2, W = kDepW<SH>, B = kDepBlock<SH>;
   extern __shared__ __align__(16) char smem[];
+  __shared__ uint32_t rcell[kDepChunk / 64][kDepRuns<SH>];
   S* v0 = reinterpret_cast<S*>(smem);
   S* v1 = v0 + TBL;
-  uint32_t* keys = reinterpret_cast<uint32_t*>(v1 + TBL);
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  S* const blocks = v1 + TBL + (size_t)wv * kDepRuns<SH> * B;  // this wavefront's
+  uint32_t* keys = reinterpret_cast<uint32_t*>(v1 + TBL + (size_t)(kDepChunk / 64) * kDepRuns<SH> * B);
   const uint32_t n = min(ctr->n[which], K.cap);
   const T diff = (T)K.diff;
-  for (uint32_t c0 = blockIdx.x * chunk; c0 < n; c0 += gridDim.x * chunk) {
-    for (int t = threadIdx.x; t < TBL; t += blockDim.x) {
-      keys[t] = kEmptyKey;
-      v0[t] = (S)0;
-      v1[t] = (S)0;
-    }
-    __syncthreads();
-    const uint32_t c1 = min(c0 + chunk, n);
-    for (uint32_t ib = c0; ib < c1; ib += blockDim.x) {  // the same trip count in every thread
-      const uint32_t i = ib + threadIdx.x;
-      const uint32_t w = i < c1 ? a.w[i] : 0u;
-      if constexpr (SH == 1 && sizeof(T) == 4) {
-        // every lane takes part in the run sums (inactive: weight 0)
-        const bool act = w != 0u;
-        Tsc<T> sk{}, sd{};
-        int jk[3] = {0, 0, 0}, jd[3] = {0, 0, 0};
-        double qa = 0.0;
-        if (act) {
-          const uint32_t cell = a.cell[i];
-          int ci, cj, ck;
-          cell_ijk(cell, K, ci, cj, ck);
-          const T o[3] = {tp<T>(a.ox)[i], tp<T>(a.oy)[i], tp<T>(a.oz)[i]};
-          sk = tsc_at<T>(K, ci, cj, ck, o[0], o[1], o[2]);
-          jk[0] = ci; jk[1] = cj; jk[2] = ck;
-          if (mode != 0) {
-            T e[3];
-            tsc_get3<T>(ctp<T>(E4), K, sk, e);
-            const T Em = sqrt(e[0] * e[0] + e[1] * e[1] + e[2] * e[2]);
-            const T mu = Mob<T>::mu(co, Em);
-            mu_out[i] = mu;
-            qa = (double)mu * (double)w;
-            const uint64_t id = a.id[i];
-            const uint4 r = philox_block((uint32_t)id, (uint32_t)(id >> 32), K.step, TAG_PUSH, 0, K.key);
-            T nr[3];
-            NormalsF<T>::get(r, nr);
-            const T t[3] = {o[0] + diff * nr[0], o[1] + diff * nr[1], o[2] + diff * nr[2]};
-            sd = tsc_at<T>(K, ci, cj, ck, t[0], t[1], t[2]);
-            jd[0] = ci + (int)floor(t[0]); jd[1] = cj + (int)floor(t[1]); jd[2] = ck + (int)floor(t[2]);
-          }
-        }
-        if (mode == 0) {
-          tbl_tsc_runs<1, L2>(keys, v0, v1, K, sk, act, jk[0], jk[1], jk[2], (double)w, sig, ne);
-        } else {
-          tbl_tsc_runs<0, L2>(keys, v0, v1, K, sk, act, jk[0], jk[1], jk[2], qa, sig, ne);
-          tbl_tsc_runs<1, L2>(keys, v0, v1, K, sd, act, jd[0], jd[1], jd[2], (double)w, sig, ne);
-        }
-        continue;
-      }
-      if (!w) continue;
-      const uint32_t cell = a.cell[i];
-      int ci, cj, ck;
-      cell_ijk(cell, K, ci, cj, ck);
-      const T o[3] = {tp<T>(a.ox)[i], tp<T>(a.oy)[i], tp<T>(a.oz)[i]};
+  for (int t = threadIdx.x; t < TBL; t += kDepChunk) {
+    keys[t] = kEmptyKey;
+    v0[t] = (S)0;
+    v1[t] = (S)0;
+  }
+  __syncthreads();
+  for (uint32_t c0 = blockIdx.x * kDepChunk; c0 < n; c0 += gridDim.x * kDepChunk) {
+    const uint32_t i = c0 + threadIdx.x, il = min(i, n - 1u);
+    uint32_t w = a.w[il], cell = a.cell[il];
+    const T o[3] = {tp<T>(a.ox)[il], tp<T>(a.oy)[il], tp<T>(a.oz)[il]};
+    const uint64_t id = mode != 0 ? a.id[il] : 0ull;
+    if (i >= n) w = 0u;
+    const bool act = w != 0u;
+    if (!act) cell = kInvalidCell;
+    const uint32_t prev = dpp_from_prev(cell, ~cell);  // lane 0: not its cell
+    const uint64_t heads = __ballot(act && prev != cell);
+    const int runs = __popcll(heads);
+    const bool dense = runs <= kDepDense;  // wave-uniform
+    const uint64_t upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
+    const int run = __popcll(heads & upto) - 1;
+    int ci = 0, cj = 0, ck = 0;
+    if (act) cell_ijk(cell, K, ci, cj, ck);
+    T pos[3] = {o[0], o[1], o[2]};
+    double qs = 0.0;
+    if (mode != 0 && act) {
+      T e[3];
       if constexpr (SH == 0) {
         int i0, j0, k0;
         T fx, fy, fz;
         tent_axis<T>(ci, o[0], K.nx, i0, fx);
         tent_axis<T>(cj, o[1], K.ny, j0, fy);
         tent_axis<T>(ck, o[2], K.nz, k0, fz);
-        if (mode == 0) {
-          tbl_cic<T, L2>(keys, v0, v1, K, i0, j0, k0, fx, fy, fz, 0.0, (double)w, sig, ne);
-          continue;
-        }
-        T e[3];
         cic_get3<T>(ctp<T>(E4), K, i0, j0, k0, fx, fy, fz, e);
-        const T Em = sqrt(e[0] * e[0] + e[1] * e[1] + e[2] * e[2]);
-        const T mu = Mob<T>::mu(co, Em);
-        mu_out[i] = mu;
-        tbl_cic<T, L2>(keys, v0, v1, K, i0, j0, k0, fx, fy, fz, (double)mu * (double)w, 0.0, sig, ne);
-        const uint64_t id = a.id[i];
-        const uint4 r = philox_block((uint32_t)id, (uint32_t)(id >> 32), K.step, TAG_PUSH, 0, K.key);
-        T nr[3];
-        NormalsF<T>::get(r, nr);
-        tent_axis<T>(ci, o[0] + diff * nr[0], K.nx, i0, fx);
-        tent_axis<T>(cj, o[1] + diff * nr[1], K.ny, j0, fy);
-        tent_axis<T>(ck, o[2] + diff * nr[2], K.nz, k0, fz);
-        tbl_cic<T, L2>(keys, v0, v1, K, i0, j0, k0, fx, fy, fz, 0.0, (double)w, sig, ne);
       } else {
-        const Tsc<T> sk = tsc_at<T>(K, ci, cj, ck, o[0], o[1], o[2]);
-        if (mode == 0) {
-          tbl_tsc<T, L2>(keys, v0, v1, K, sk, 0.0, (double)w, sig, ne);
-          continue;
-        }
-        T e[3];
-        tsc_get3<T>(ctp<T>(E4), K, sk, e);
-        const T Em = sqrt(e[0] * e[0] + e[1] * e[1] + e[2] * e[2]);
-        const T mu = Mob<T>::mu(co, Em);
-        mu_out[i] = mu;
-        tbl_tsc<T, L2>(keys, v0, v1, K, sk, (double)mu * (double)w, 0.0, sig, ne);
-        const uint64_t id = a.id[i];
-        const uint4 r = philox_block((uint32_t)id, (uint32_t)(id >> 32), K.step, TAG_PUSH, 0, K.key);
-        T nr[3];
-        NormalsF<T>::get(r, nr);
-        const Tsc<T> sd = tsc_at<T>(K, ci, cj, ck, o[0] + diff * nr[0], o[1] + diff * nr[1], o[2] + diff * nr[2]);
-        tbl_tsc<T, L2>(keys, v0, v1, K, sd, 0.0, (double)w, sig, ne);
+        tsc_get3<T>(ctp<T>(E4), K, tsc_at<T>(K, ci, cj, ck, o[0], o[1], o[2]), e);
       }
+      const T Em = sqrt(e[0] * e[0] + e[1] * e[1] + e[2] * e[2]);
+      const T mu = Mob<T>::mu(co, Em);
+      mu_out[i] = mu;
+      qs = (double)mu * (double)w * A::kUnit[0];
+      const uint4 r = philox_block((uint32_t)id, (uint32_t)(id >> 32), K.step, TAG_PUSH, 0, K.key);
+      T nr[3];
+      NormalsF<T>::get(r, nr);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) pos[q] = o[q] + diff * nr[q];
+    }
+    const double qn = (double)w * A::kUnit[1];
+    // contributions small enough for the short conversion, in every lane of the wavefront
+    const bool fits = __ballot(!(qs < 0x1p52 && qn < 0x1p52)) == 0ull;
+#pragma unroll 1
+    for (int r0 = 0; r0 < runs; r0 += kDepRuns<SH>) {
+      const int nr = min(runs - r0, kDepRuns<SH>);
+      for (int t = lane; t < nr * B; t += 64) blocks[t] = (S)0;
+      wave_lds_sync();
+      if (act && run >= r0 && run < r0 + kDepRuns<SH>) {
+        S* const blk = blocks + (run - r0) * B;
+        if ((heads >> lane) & 1ull) rcell[wv][run - r0] = cell;
+#pragma unroll 1
+        for (int f = mode != 0 ? 0 : 1; f < 2; ++f) {  // conductivity at X^k, electrons at X_dagger
+          const T t[3] = {f ? pos[0] : o[0], f ? pos[1] : o[1], f ? pos[2] : o[2]};
+          const double q = f ? qn : qs;
+          S* const bf = f ? blk + 27 : blk;
+          if constexpr (SH == 0) {
+            int i0, j0, k0;
+            T fx, fy, fz;
+            tent_axis<T>(ci, t[0], K.nx, i0, fx);
+            tent_axis<T>(cj, t[1], K.ny, j0, fy);
+            tent_axis<T>(ck, t[2], K.nz, k0, fz);
+            const Corner<T> c = corners<T>(lane, fx, fy, fz);
+            const unsigned dx = (unsigned)(i0 - ci + 1), dy = (unsigned)(j0 - cj + 1), dz = (unsigned)(k0 - ck + 1);
+            if (dx < 2u && dy < 2u && dz < 2u)
+              blk_cic<T, 3>(bf + dx + 3 * (dy + 3 * dz), c, q, fits);
+            else
+              tbl_cic<T, L2>(keys, f ? v1 : v0, K, i0, j0, k0, c, q, fits, f ? ne : sig);
+          } else {
+            const int wf = f ? W : 3;
+            const T reach = f ? (T)1 : (T)0;
+            const Tsc<T> s = tsc_at<T>(K, ci, cj, ck, t[0], t[1], t[2]);
+            const T bx = floor(t[0]), by = floor(t[1]), bz = floor(t[2]);
+            if (fabs(bx) <= reach && fabs(by) <= reach && fabs(bz) <= reach)
+              blk_tsc<T>(bf + ((int)bx + f) + wf * (((int)by + f) + wf * ((int)bz + f)), wf, lane, s, q, fits);
+            else
+              tbl_tsc<T, L2>(keys, f ? v1 : v0, K, s, q, fits, f ? ne : sig);
+          }
+        }
+      }
+      wave_lds_sync();
+      // the runs' blocks to the table or the grid, one node and field per lane; a node
+      // outside the grid belongs to the wall cell (TSC; CIC leaves nothing there)
+      for (int t = lane; t < nr * B; t += 64) {
+        const S e = blocks[t];
+        if (e == (S)0) continue;
+        const int r = t / B, u = t - r * B;
+        int ri, rj, rk;
+        cell_ijk(rcell[wv][r], K, ri, rj, rk);
+        const bool f = u >= 27;
+        int lx, ly, lz;
+        if (W == 3 || !f) {
+          const int q = f ? u - 27 : u;
+          lz = q / 9;
+          ly = (q - 9 * lz) / 3;
+          lx = q - 9 * lz - 3 * ly;
+          lx -= 1; ly -= 1; lz -= 1;
+        } else {
+          const int q = u - 27;
+          lz = q / (W * W);
+          ly = (q - W * W * lz) / W;
+          lx = q - W * W * lz - W * ly;
+          lx -= W / 2; ly -= W / 2; lz -= W / 2;
+        }
+        const int x = min(max(ri + lx, 0), K.nx - 1), y = min(max(rj + ly, 0), K.ny - 1),
+                  z = min(max(rk + lz, 0), K.nz - 1);
+        const uint32_t row = (uint32_t)y + (uint32_t)K.ny * (uint32_t)z;
+        const uint32_t node = (uint32_t)x + (uint32_t)K.nx * row;
+        S* const g = f ? ne : sig;
+        if (dense) tbl_put<S, L2>(keys, f ? v1 : v0, node, tbl_slot<L2>((uint32_t)x, row), e, g);
+        else atomicAdd(&g[node], e);
+      }
+      wave_lds_sync();
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < TBL; t += blockDim.x) {
+    for (int t = threadIdx.x; t < TBL; t += kDepChunk) {
       const uint32_t k = keys[t];
       if (k == kEmptyKey) continue;
-      if (v0[t] != (S)0) atomicAdd(&sig[k], v0[t]);
-      if (v1[t] != (S)0) atomicAdd(&ne[k], v1[t]);
+      const S e0 = v0[t], e1 = v1[t];
+      if (e0 != (S)0) atomicAdd(&sig[k], e0);
+      if (e1 != (S)0) atomicAdd(&ne[k], e1);
+      keys[t] = kEmptyKey;
+      v0[t] = (S)0;
+      v1[t] = (S)0;
     }
     __syncthreads();
   }
@@ -2517,18 +2565,14 @@ static int deposit_and_solve(itokmc_ctx* ctx, FieldState* F, const StepConst& K,
   const void* Eo = F->E[F->cur];
   phase_begin(ctx, PH_DEPOSIT);  // the deposit kernel alone
   {
-    constexpr int L2 = DepTbl<T>::log2n;
-    const size_t lds = (size_t)(1 << L2) * (4 + 2 * sizeof(S));
     int g = (int)((ctx->cap + kDepChunk - 1) / kDepChunk);
     g = g < 1 ? 1 : (g > 16384 ? 16384 : g);
     if (ctx->d.shape == ITOKMC_SHAPE_TSC)
-      k_field_deposit_lds<T, L2, 1><<<g, 256, lds, s>>>(ctx->bank[ctx->cur], ctx->ctr, ctx->cur, K, Eo,
-                                                        coef(ctx), mode, (S*)F->sig, (S*)F->ne,
-                                                        (uint32_t)kDepChunk, (T*)ctx->mu_p);
+      k_field_deposit_lds<T, 1><<<g, 256, dep_lds_bytes<T, 1>(), s>>>(
+          ctx->bank[ctx->cur], ctx->ctr, ctx->cur, K, Eo, coef(ctx), mode, (S*)F->sig, (S*)F->ne, (T*)ctx->mu_p);
     else
-      k_field_deposit_lds<T, L2, 0><<<g, 256, lds, s>>>(ctx->bank[ctx->cur], ctx->ctr, ctx->cur, K, Eo,
-                                                        coef(ctx), mode, (S*)F->sig, (S*)F->ne,
-                                                        (uint32_t)kDepChunk, (T*)ctx->mu_p);
+      k_field_deposit_lds<T, 0><<<g, 256, dep_lds_bytes<T, 0>(), s>>>(
+          ctx->bank[ctx->cur], ctx->ctr, ctx->cur, K, Eo, coef(ctx), mode, (S*)F->sig, (S*)F->ne, (T*)ctx->mu_p);
   }
   phase_end(ctx, PH_DEPOSIT);
   phase_begin(ctx, PH_FIELD_PREP);
