@@ -17,6 +17,8 @@
 
 #include <type_traits>
 
+#include <algorithm>
+
 #include "device.hpp"
 #include "itk.hpp"
 #include "couple_device.hpp"
@@ -188,9 +190,10 @@ hipError_t launch_couple(itokmc_ctx* ctx, const StepConst& k) {
   const int dest = 1 - ctx->cur;  // coupling acts on the freshly binned bank
   const bool f64 = ctx->d.precision == ITOKMC_FP64;
   int gl = (int)((ctx->ncell + 255) / 256);
-  // at most 768 workgroups (three per CU), each looping over the queue: 0.096 ms per
-  // step at 9.5e6 particles against 0.21 ms with 4096 and 0.125 ms with 256
-  gl = gl < 1 ? 1 : (gl > 768 ? 768 : gl);
+  // at most 2048 workgroups (eight per CU), each looping over the queue: 36 us per step at
+  // 6e6 particles against 40 with 768, 46 against 57 at 5.5e7 (while the tallies shared one
+  // line, more workgroups meant more waiting for it)
+  gl = gl < 1 ? 1 : (gl > 2048 ? 2048 : gl);
   if (f64)
     k_couple_light<double><<<gl, 256, 0, ctx->s>>>(ctx->bank[dest], ctx->ctr, k, ctx->work, ctx->occ,
                                                    ctx->start, ctx->dN, ctx->cbase, ctx->d.n_new,
@@ -203,12 +206,15 @@ hipError_t launch_couple(itokmc_ctx* ctx, const StepConst& k) {
   phase_end(ctx, PH_COUPLE_LIGHT);
   if (el != hipSuccess) return el;
   phase_begin(ctx, PH_COUPLE);  // the wavefront-per-cell kernel alone
-  // a grid of 32768 one-wavefront workgroups (128 per CU), each taking every 32768th
-  // queued cell: measured at 1.82 ms per launch at 9.5e6 particles, against 2.17 ms with
-  // 65536, 3.5 ms with 131072 and 2.05 ms with 10240 workgroups (28672-49152 all within
-  // 1%)
-  int g = (int)(ctx->ncell < 32768u ? ctx->ncell : 32768u);
-  if (g < 1) g = 1;
+  // One wavefront per workgroup, each taking every g-th queued cell.  With merging nearly
+  // every dense cell is queued: 131072 wavefronts, 8 cells of the grid each, even out the
+  // cells' costs (0.81 -> 0.76 ms per launch at 6e6 particles, 6.58 -> 6.28 ms at 4.5e7
+  // against 32768); a grid of up to 2^18 cells keeps up to 32768 (0.163 ms at 64^3, 4e5
+  // particles; 8192: 0.187).  Without merging only large cells that lose particles come
+  // here and the launch is mostly empty: 4096 (32^3: 8.4 -> 4.2 us).
+  const uint32_t nc = ctx->ncell;
+  const int g = (int)std::max(1u, ctx->d.n_ppc > 0 ? std::min({nc, std::max(32768u, nc / 8u), 131072u})
+                                                   : std::min(nc, 4096u));
   const int nl = merge_leaves(ctx->d.n_ppc);
   auto wave = [&](auto tt, auto nlt) {
     using T = decltype(tt);

@@ -437,10 +437,11 @@ hipError_t launch_kmc_step(itokmc_ctx* ctx, const StepConst& k, const FieldRates
         ctx->occ_fires, ctx->dN, ctx->work, ctx->cbase, fr, qa, ctx->d.n_new, dest);
     return hipGetLastError();
   }
-  // at most 256 workgroups (one per CU), each looping over its share of the occupied
-  // cells: measured 0.23 ms per step at 9.5e6 particles against 0.28 ms with 4096
+  // at most 512 workgroups (two per CU), each looping over its share of the occupied
+  // cells: 0.197 ms per step at 5.5e7 particles in 7e6 cells against 0.306 with 256 and
+  // 0.202 with 1024; 0.215 against 0.307 and 0.219 at 4.5e7 in 3e6
   int g = (int)((ctx->ncell + 256 * kKmcPer - 1) / (256 * kKmcPer));
-  if (g > 256) g = 256;
+  if (g > 512) g = 512;
   if (g < 1) g = 1;
   const int qa = ctx->d.n_ppc > 0 ? 1 : 0, dest = 1 - ctx->cur;
   k_kmc_step<true><<<g, 256, 0, ctx->s>>>(params(ctx), k, ctx->ctr, ctx->occ, ctx->cellacc, ctx->nplus,

@@ -723,9 +723,9 @@ hipError_t launch_count(itokmc_ctx* ctx) {
 
 hipError_t launch_photons(itokmc_ctx* ctx, const StepConst& k) {
   if (!(ctx->c.kgamma_ratio > 0.0)) return hipSuccess;
-  // up to 4096 workgroups: 0.149 ms per step at 9.5e6 particles against 0.21 ms with
-  // 16384 and 0.17 ms with 2048
-  const int g = grid_for(ctx->ncell, kBlock, 4096);
+  // up to 8192 workgroups: 0.67 ms per step at 4.5e7 particles against 0.76 ms with 4096
+  // and 0.64 ms with 16384; 0.107 against 0.113 and 0.113 ms at 6e6
+  const int g = grid_for(ctx->ncell, kBlock, 8192);
   if (fp64(ctx))
     k_photons<double><<<g, kBlock, 0, ctx->s>>>(ctx->bank[ctx->cur], ctx->ctr, ctx->cur,
                                                  ctx->cellacc, ctx->tiles, ctx->ngamma, ctx->nplus, k,
