@@ -67,7 +67,9 @@ __device__ __forceinline__ void load_field(const FieldRates& fr, uint32_t c, dou
 // settles those whose step is a single SSA excursion with a small register footprint;
 // it queues the rest, untouched, for the full pass (!kFast), which runs the complete
 // method from the same state and stream (with the rates the fast pass computed).
-// A thread takes kKmcPer cells between the workgroup-aggregated appends to the queues.
+// A thread takes kKmcPer cells between the workgroup-aggregated appends to the queues, and
+// fewer where the launch has threads for that: a small launch is as long as one thread's
+// chain of excursions (a 32^3 avalanche: 15.7 -> 10.9 us, 128^3: 19.1 -> 15.6 us).
 constexpr int kKmcPer = 4;
 
 template <bool kFast>
@@ -79,7 +81,9 @@ __global__ void __launch_bounds__(kFast ? 256 : 64) k_kmc_step(
   if (ctr->halt) return;
   __shared__ uint32_t sh[18];
   const uint32_t n = kFast ? ctr->n_occ : ctr->n_heavy;
-  const uint32_t span = blockDim.x * kKmcPer;
+  const uint32_t all = gridDim.x * blockDim.x;
+  const uint32_t per = n >= kKmcPer * all ? (uint32_t)kKmcPer : (n + all - 1) / all;
+  const uint32_t span = blockDim.x * per;
   uint64_t t0 = 0, t1 = 0, t2 = 0;
   for (uint32_t base = blockIdx.x * span; base < n; base += gridDim.x * span) {
     uint32_t js[kKmcPer], Ms[kKmcPer], fl[kKmcPer];  // fl: 1 queue, 2 defer
@@ -122,7 +126,7 @@ __global__ void __launch_bounds__(kFast ? 256 : 64) k_kmc_step(
     for (int r = 0; r < kKmcPer; ++r) {
       const uint32_t jj = base + (uint32_t)r * blockDim.x + threadIdx.x;
       Ms[r] = 0; fl[r] = 0;
-      if (jj >= n) continue;
+      if (r >= (int)per || jj >= n) continue;
       const uint32_t j = js[r];
       const uint32_t c = cs[r];
       const uint32_t Xe = xe0[r];
@@ -440,7 +444,7 @@ hipError_t launch_kmc_step(itokmc_ctx* ctx, const StepConst& k, const FieldRates
   // at most 512 workgroups (two per CU), each looping over its share of the occupied
   // cells: 0.197 ms per step at 5.5e7 particles in 7e6 cells against 0.306 with 256 and
   // 0.202 with 1024; 0.215 against 0.307 and 0.219 at 4.5e7 in 3e6
-  int g = (int)((ctx->ncell + 256 * kKmcPer - 1) / (256 * kKmcPer));
+  int g = (int)((ctx->ncell + 255) / 256);
   if (g > 512) g = 512;
   if (g < 1) g = 1;
   const int qa = ctx->d.n_ppc > 0 ? 1 : 0, dest = 1 - ctx->cur;
@@ -449,7 +453,7 @@ hipError_t launch_kmc_step(itokmc_ctx* ctx, const StepConst& k, const FieldRates
                                           ctx->cbase, ctx->heavy, ctx->rates, fr, qa, ctx->d.n_new, dest);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  int gh = (int)((ctx->ncell + 64 * kKmcPer - 1) / (64 * kKmcPer));
+  int gh = (int)((ctx->ncell + 63) / 64);
   if (gh > 4096) gh = 4096;
   if (gh < 1) gh = 1;
   k_kmc_step<false><<<gh, 64, 0, ctx->s>>>(params(ctx), k, ctx->ctr, ctx->occ, ctx->cellacc, ctx->nplus,

@@ -156,9 +156,12 @@ __global__ void __launch_bounds__(kBlock) k_push_uniform(Bank a, Counters* ctr, 
   uint64_t out_w = 0, pushed = 0;
   const int lim[3] = {k.nx, k.ny, k.nz};
   // two particles per thread (a workgroup-sized stride apart, so that loads stay
-  // coalesced): both particles' words are requested before either is pushed
-  for (uint32_t base = blockIdx.x * blockDim.x * 2u; base < n; base += gridDim.x * blockDim.x * 2u) {
-    uint32_t ii[2] = {base + threadIdx.x, base + blockDim.x + threadIdx.x};
+  // coalesced): both particles' words are requested before either is pushed.  One where the
+  // grid has a thread for each: a small launch is as long as one thread's chain (a 32^3
+  // avalanche: 9.2 -> 7.0 us)
+  const uint32_t span = n > gridDim.x * blockDim.x ? 2u * blockDim.x : blockDim.x;
+  for (uint32_t base = blockIdx.x * span; base < n; base += gridDim.x * span) {
+    uint32_t ii[2] = {base + threadIdx.x, span > blockDim.x ? base + blockDim.x + threadIdx.x : n};
     uint32_t w[2] = {0, 0}, cell[2] = {0, 0};
     uint64_t id[2] = {0, 0};
     T o[2][3] = {{(T)0, (T)0, (T)0}, {(T)0, (T)0, (T)0}};
@@ -329,12 +332,17 @@ __global__ void __launch_bounds__(kBlock) k_photons(Bank a, Counters* ctr, int w
 // totals (top), then per cell the first bank slot (start, written for occupied cells
 // only) and the ascending list of occupied cells (down).  Scratch layout (u32):
 // tile counts [2 nb] | tile prefixes within the group [2 nb] | group prefixes [2 ng + 2].
+// Up to kScanSmall tiles (2^21 cells: four counts per thread) the down pass sums
+// the tile counts before its own itself and mid and top are not launched: a step of a 32^3
+// avalanche is a chain of a dozen launches of 4-15 us each, and these two took 4.8 us (6.6
+// at 128^3), where the sum in every workgroup of the down pass adds 1.2 (2.4 at 128^3).
 
 constexpr int kScanPer = 8;                     // cells per thread (k_scan_down unpacks two uint4)
 constexpr int kScanTile = kBlock * kScanPer;    // cells per tile (1 << kTileShift)
 static_assert(kScanTile == (1 << kTileShift), "scan tile and tile flags disagree");
 static_assert(kScanPer == 8, "k_scan_down reads a thread's counts as two uint4");
 constexpr int kScanGroup = 1024;                // tiles per mid-level group
+constexpr int kScanSmall = 4 * kBlock;          // tiles up to which down sums the tile counts
 
 template <int NT>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* sh, uint32_t* total) {
@@ -436,6 +444,7 @@ __global__ void __launch_bounds__(kScanGroup) k_scan_top(uint32_t* grp, uint32_t
   if (threadIdx.x == 0) { grp[2 * ng] = s0; grp[2 * ng + 1] = s1; }
 }
 
+template <bool kSmall>
 __global__ void __launch_bounds__(kBlock) k_scan_down(const unsigned long long* cellacc,
                                                      uint32_t ncell_arg, const uint32_t* ncell_dev,
                                                      const uint32_t* cnt, const uint32_t* pre,
@@ -446,6 +455,27 @@ __global__ void __launch_bounds__(kBlock) k_scan_down(const unsigned long long* 
   __shared__ __align__(16) uint32_t tile_n[kScanTile];
   const uint32_t ncell = scan_cells(ncell_arg, ncell_dev);
   const uint32_t nb = scan_tiles(ncell);
+  // kSmall (one tile per workgroup): particles (low word) and occupied cells (high) of the
+  // tiles before this one, and of all of them in workgroup 0
+  uint64_t before = 0, all = 0;
+  if (kSmall) {
+    __shared__ uint64_t part[2][kBlock / 64];
+    for (uint32_t i = threadIdx.x; i < nb; i += kBlock) {
+      const uint2 v = reinterpret_cast<const uint2*>(cnt)[i];
+      const uint64_t x = ((uint64_t)v.y << 32) | v.x;
+      all += x;
+      if (i < blockIdx.x) before += x;
+    }
+    all = wave_sum64(all);
+    before = wave_sum64(before);
+    if (lane_id() == 0) {
+      part[0][threadIdx.x >> 6] = before;
+      part[1][threadIdx.x >> 6] = all;
+    }
+    __syncthreads();
+    before = part[0][0] + part[0][1] + part[0][2] + part[0][3];
+    all = part[1][0] + part[1][1] + part[1][2] + part[1][3];
+  }
   for (uint32_t t = blockIdx.x; t < nb; t += gridDim.x) {
     if (cnt[2 * t] == 0u) continue;  // empty tile: no start entries, no occupied cells
     // counts read in coalesced order through LDS; each thread then takes eight
@@ -471,8 +501,9 @@ __global__ void __launch_bounds__(kBlock) k_scan_down(const unsigned long long* 
     }
     const uint32_t g = t / kScanGroup;
     uint32_t t0, t1;
-    uint32_t p0 = block_exclusive_scan<kBlock>(k, sh[0], &t0) + pre[2 * t] + grp[2 * g];
-    uint32_t p1 = block_exclusive_scan<kBlock>(oc, sh[1], &t1) + pre[2 * t + 1] + grp[2 * g + 1];
+    uint32_t p0 = block_exclusive_scan<kBlock>(k, sh[0], &t0) + (kSmall ? (uint32_t)before : pre[2 * t] + grp[2 * g]);
+    uint32_t p1 =
+        block_exclusive_scan<kBlock>(oc, sh[1], &t1) + (kSmall ? (uint32_t)(before >> 32) : pre[2 * t + 1] + grp[2 * g + 1]);
 #pragma unroll
     for (int j = 0; j < kScanPer; ++j) {
       if (n[j]) {
@@ -484,7 +515,7 @@ __global__ void __launch_bounds__(kBlock) k_scan_down(const unsigned long long* 
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     const uint32_t ng = (nb + kScanGroup - 1) / kScanGroup;
-    const uint32_t total = grp[2 * ng], tocc = grp[2 * ng + 1];
+    const uint32_t total = kSmall ? (uint32_t)all : grp[2 * ng], tocc = kSmall ? (uint32_t)(all >> 32) : grp[2 * ng + 1];
     start[ncell] = total;
     ctr->sorted = total;
     ctr->n_occ = tocc;
@@ -753,9 +784,13 @@ hipError_t launch_scan_raw(const unsigned long long* cellacc, uint32_t max_cells
   const uint32_t gt = std::max<uint32_t>(1, std::min<uint32_t>(nb, 8192));  // tiles are looped over
   const uint32_t ng = std::max<uint32_t>(1, (nb + kScanGroup - 1) / kScanGroup);
   k_scan_reduce<<<gt, kBlock, 0, s>>>(cellacc, max_cells, ncell_dev, tiles, cnt);
+  if (nb <= kScanSmall) {
+    k_scan_down<true><<<gt, kBlock, 0, s>>>(cellacc, max_cells, ncell_dev, cnt, pre, grp, start, occ, ctr, dest);
+    return hipGetLastError();
+  }
   k_scan_mid<<<std::min<uint32_t>(ng, 1024), kScanGroup, 0, s>>>(cnt, pre, grp, max_cells, ncell_dev);
   k_scan_top<<<1, kScanGroup, 0, s>>>(grp, max_cells, ncell_dev);
-  k_scan_down<<<gt, kBlock, 0, s>>>(cellacc, max_cells, ncell_dev, cnt, pre, grp, start, occ, ctr, dest);
+  k_scan_down<false><<<gt, kBlock, 0, s>>>(cellacc, max_cells, ncell_dev, cnt, pre, grp, start, occ, ctr, dest);
   return hipGetLastError();
 }
 
