@@ -402,10 +402,14 @@ template <> struct DepAcc<float> {
 //   to the grid directly, a node per lane: a row of a block is one request of the global
 //   atomics (25e9 lines of 64 B a second, whatever they hold), where a particle by itself
 //   is one request per node.
-// * A particle displaced out of its block adds to the table by itself.
+// * A particle displaced out of its block adds to the table by itself.  So does, with CIC in
+//   double precision or with fewer than kDepFew particles, one of a wavefront of more than kDepRuns runs: such a
+//   launch is as long as one wavefront, and eight batches of blocks after each other take
+//   longer than eight insertions (128^3 request 34 against 28 us, 64^3 in double precision,
+//   4e5 particles, 104 against 93); with all CUs busy the requests count instead (1.86
+//   against 2.02 ms at 4.5e7, 0.36 against 0.39 at 6e6).
 //
-// A block stays worth its zeroing and its flush down to single particles, so every
-// wavefront takes this way; the table takes the blocks of at most kDepDense runs (of 2 or
+// The table takes the blocks of at most kDepDense runs (of 2 or
 // 64 instead of 8: 2.92 and 3.25 ms where 8 takes 1.88, 4.5e7 particles).  CIC in single
 // precision: 512 entries (24 KB with the blocks) and 79 VGPRs let six workgroups of a CU
 // overlap their loads; 1024 entries leave four (2.37 ms).  What bounds it is that latency:
@@ -413,12 +417,13 @@ template <> struct DepAcc<float> {
 // lane added its own contributions to a table of 1024 entries (TSC: sums over runs by
 // segmented scans first): CIC 2.15 ms at 4.5e7 particles, 0.40 -> 0.37 ms at 6.3e6; TSC
 // 1.45 -> 0.74 ms at 3.7e6 (the same table, overfull with the nodes of single particles,
-// and 2.5e7 -> 1.3e7 global requests at the end of a run).  Double precision 0.10 ms at
-// 4e5 particles either way.
+// and 2.5e7 -> 1.3e7 global requests at the end of a run).  Double precision 96 -> 93 us
+// at 4e5 particles.
 constexpr int kDepChunk = 256;
 constexpr int kDepProbes = 8;
 template <int SH> constexpr int kDepRuns = SH == 0 ? 8 : 4;  // 4: 2.01 ms, 16: 2.21 (CIC)
 constexpr int kDepDense = 8;
+constexpr uint32_t kDepFew = 1u << 20;
 constexpr uint32_t kEmptyKey = 0xFFFFFFFFu;
 template <typename T, int SH> constexpr int kDepL2 = SH == 0 && sizeof(T) == 4 ? 9 : 10;
 // Nodes per axis of a run's block of the displaced charge.
@@ -622,14 +627,15 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? 6 : 4) : (SH 
     const double qn = (double)w * A::kUnit[1];
     // contributions small enough for the short conversion, in every lane of the wavefront
     const bool fits = __ballot(!(qs < 0x1p52 && qn < 0x1p52)) == 0ull;
+    const bool single = SH == 0 && runs > kDepRuns<SH> && (sizeof(T) == 8 || n < kDepFew);  // wave-uniform
 #pragma unroll 1
-    for (int r0 = 0; r0 < runs; r0 += kDepRuns<SH>) {
-      const int nr = min(runs - r0, kDepRuns<SH>);
+    for (int r0 = 0; r0 < runs; r0 += single ? 64 : kDepRuns<SH>) {
+      const int nr = single ? 0 : min(runs - r0, kDepRuns<SH>);
       for (int t = lane; t < nr * B; t += 64) blocks[t] = (S)0;
       wave_lds_sync();
-      if (act && run >= r0 && run < r0 + kDepRuns<SH>) {
-        S* const blk = blocks + (run - r0) * B;
-        if ((heads >> lane) & 1ull) rcell[wv][run - r0] = cell;
+      if (act && (single || (run >= r0 && run < r0 + kDepRuns<SH>))) {
+        S* const blk = blocks + (single ? 0 : run - r0) * B;
+        if (!single && (heads >> lane) & 1ull) rcell[wv][run - r0] = cell;
 #pragma unroll 1
         for (int f = mode != 0 ? 0 : 1; f < 2; ++f) {  // conductivity at X^k, electrons at X_dagger
           const T t[3] = {f ? pos[0] : o[0], f ? pos[1] : o[1], f ? pos[2] : o[2]};
@@ -643,7 +649,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? 6 : 4) : (SH 
             tent_axis<T>(ck, t[2], K.nz, k0, fz);
             const Corner<T> c = corners<T>(lane, fx, fy, fz);
             const unsigned dx = (unsigned)(i0 - ci + 1), dy = (unsigned)(j0 - cj + 1), dz = (unsigned)(k0 - ck + 1);
-            if (dx < 2u && dy < 2u && dz < 2u)
+            if (!single && dx < 2u && dy < 2u && dz < 2u)
               blk_cic<T, 3>(bf + dx + 3 * (dy + 3 * dz), c, q, fits);
             else
               tbl_cic<T, L2>(keys, f ? v1 : v0, K, i0, j0, k0, c, q, fits, f ? ne : sig);

@@ -73,3 +73,24 @@ def test_runs(itk, orc, prec, tol, shape, disp):
             assert np.array_equal(phi, other)
         else:
             assert np.abs(phi - other).max() <= tol * np.abs(phi_o).max()
+
+
+@pytest.mark.parametrize("shape", ["cic", "tsc"])
+def test_many_particles_in_any_order(itk, shape):
+    """Past 2^20 particles (CIC's other line): grouped by cell and shuffled, bit for bit."""
+    cfg = _streamer_small(grid=GRID, shape=shape, precision="fp32", n_ppc=0, gmg_rtol=1e-12, gmg_max_cycles=500)
+    rng = np.random.default_rng(91)
+    n, nc = (1 << 20) + 4321, int(np.prod(GRID))
+    cells = np.sort(rng.integers(0, nc, n))
+    off = rng.random((n, 3))
+    w = rng.integers(1, 4, n).astype(np.uint32)
+    ids = np.arange(1, n + 1, dtype=np.uint64)
+    plus = np.bincount(cells, weights=w, minlength=nc).astype(np.uint32)
+    phi = []
+    for order in (np.arange(n), rng.permutation(n)):
+        g = itk.Sim(cfg, precision="fp32", max_particles=2 * n)
+        g.set_particles(cells[order], off[order], w[order], ids[order])
+        g.set_counts("plus", plus)
+        g.transport(cfg["dt"])
+        phi.append(g.field())
+    assert np.array_equal(phi[0], phi[1])
