@@ -403,11 +403,16 @@ template <> struct DepAcc<float> {
 //   atomics (25e9 lines of 64 B a second, whatever they hold), where a particle by itself
 //   is one request per node.
 // * A particle displaced out of its block adds to the table by itself.  So does, with CIC in
-//   double precision or with fewer than kDepFew particles, one of a wavefront of more than kDepRuns runs: such a
-//   launch is as long as one wavefront, and eight batches of blocks after each other take
-//   longer than eight insertions (128^3 request 34 against 28 us, 64^3 in double precision,
-//   4e5 particles, 104 against 93); with all CUs busy the requests count instead (1.86
-//   against 2.02 ms at 4.5e7, 0.36 against 0.39 at 6e6).
+//   double precision, one of a wavefront of more than kDepRuns runs (64^3, 4e5 particles:
+//   104 against 93 us).
+//
+// kLanes (CIC in single precision): every particle adds to a table of 1024 entries by
+// itself, without blocks.  It takes launches of fewer than kDepFew particles, which are as
+// long as one wavefront (128^3 request 34 against 29 us), and those of fewer than kDepFull
+// particles per occupied cell, where the wavefronts of many runs would go through batches of
+// blocks after each other (1.0e7 particles in 3.3e6 cells 1.12 ms against 0.97, 1.3e7 1.72
+// against 1.31; 6e6 in 3.2e5 0.29 against 0.32, 4.5e7 in 2.2e6 1.86 against 2.15).  The
+// counts are on the device, so both kernels are launched and one returns (3-5 us).
 //
 // The table takes the blocks of at most kDepDense runs (of 2 or
 // 64 instead of 8: 2.92 and 3.25 ms where 8 takes 1.88, 4.5e7 particles).  CIC in single
@@ -423,16 +428,17 @@ constexpr int kDepChunk = 256;
 constexpr int kDepProbes = 8;
 template <int SH> constexpr int kDepRuns = SH == 0 ? 8 : 4;  // 4: 2.01 ms, 16: 2.21 (CIC)
 constexpr int kDepDense = 8;
-constexpr uint32_t kDepFew = 1u << 20;
+constexpr uint32_t kDepFew = 1u << 21;
 constexpr uint32_t kEmptyKey = 0xFFFFFFFFu;
-template <typename T, int SH> constexpr int kDepL2 = SH == 0 && sizeof(T) == 4 ? 9 : 10;
+template <typename T, int SH, bool kLanes> constexpr int kDepL2 = SH == 0 && sizeof(T) == 4 && !kLanes ? 9 : 10;
+constexpr uint32_t kDepFull = 12;
 // Nodes per axis of a run's block of the displaced charge.
 template <int SH> constexpr int kDepW = SH == 0 ? 3 : 5;
 template <int SH> constexpr int kDepBlock = 27 + kDepW<SH> * kDepW<SH> * kDepW<SH>;
-template <typename T, int SH>
+template <typename T, int SH, bool kLanes>
 constexpr size_t dep_lds_bytes() {
-  return ((size_t)1 << kDepL2<T, SH>) * (4 + 2 * sizeof(typename DepAcc<T>::S)) +
-         (size_t)(kDepChunk / 64) * kDepRuns<SH> * kDepBlock<SH> * sizeof(typename DepAcc<T>::S);
+  return ((size_t)1 << kDepL2<T, SH, kLanes>) * (4 + 2 * sizeof(typename DepAcc<T>::S)) +
+         (kLanes ? (size_t)0 : (size_t)(kDepChunk / 64) * kDepRuns<SH> * kDepBlock<SH> * sizeof(typename DepAcc<T>::S));
 }
 
 // Slot of a node in the table: the row hashed, x kept in order, so that a row's nodes sit
@@ -562,21 +568,25 @@ __device__ __forceinline__ void blk_tsc(typename DepAcc<T>::S* blk, int W, int l
       }
 }
 
-template <typename T, int SH>
-__global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? 6 : 4) : (SH == 0 ? 4 : 1))
+template <typename T, int SH, bool kLanes>
+__global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? (kLanes ? 7 : 6) : 4) : (SH == 0 ? 4 : 1))
     k_field_deposit_lds(Bank a, const Counters* ctr, int which, StepConst K, const void* E4, Coef co, int mode,
                         typename DepAcc<T>::S* sig, typename DepAcc<T>::S* ne, T* mu_out) {
   using A = DepAcc<T>;
   using S = typename A::S;
-  constexpr int L2 = kDepL2<T, SH>, TBL = 1 << L2, W = kDepW<SH>, B = kDepBlock<SH>;
+  constexpr int L2 = kDepL2<T, SH, kLanes>, TBL = 1 << L2, W = kDepW<SH>, B = kDepBlock<SH>;
   extern __shared__ __align__(16) char smem[];
   __shared__ uint32_t rcell[kDepChunk / 64][kDepRuns<SH>];
   S* v0 = reinterpret_cast<S*>(smem);
   S* v1 = v0 + TBL;
   const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   S* const blocks = v1 + TBL + (size_t)wv * kDepRuns<SH> * B;  // this wavefront's
-  uint32_t* keys = reinterpret_cast<uint32_t*>(v1 + TBL + (size_t)(kDepChunk / 64) * kDepRuns<SH> * B);
+  uint32_t* keys = reinterpret_cast<uint32_t*>(v1 + TBL + (kLanes ? 0 : (kDepChunk / 64) * kDepRuns<SH> * B));
   const uint32_t n = min(ctr->n[which], K.cap);
+  if constexpr (SH == 0 && sizeof(T) == 4) {
+    const bool lanes = n < kDepFew || n / kDepFull < ctr->n_occ;
+    if (lanes != kLanes) return;
+  }
   const T diff = (T)K.diff;
   for (int t = threadIdx.x; t < TBL; t += kDepChunk) {
     keys[t] = kEmptyKey;
@@ -627,7 +637,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? 6 : 4) : (SH 
     const double qn = (double)w * A::kUnit[1];
     // contributions small enough for the short conversion, in every lane of the wavefront
     const bool fits = __ballot(!(qs < 0x1p52 && qn < 0x1p52)) == 0ull;
-    const bool single = SH == 0 && runs > kDepRuns<SH> && (sizeof(T) == 8 || n < kDepFew);  // wave-uniform
+    const bool single = kLanes || (SH == 0 && sizeof(T) == 8 && runs > kDepRuns<SH>);  // wave-uniform
 #pragma unroll 1
     for (int r0 = 0; r0 < runs; r0 += single ? 64 : kDepRuns<SH>) {
       const int nr = single ? 0 : min(runs - r0, kDepRuns<SH>);
@@ -647,7 +657,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? 6 : 4) : (SH 
             tent_axis<T>(ci, t[0], K.nx, i0, fx);
             tent_axis<T>(cj, t[1], K.ny, j0, fy);
             tent_axis<T>(ck, t[2], K.nz, k0, fz);
-            const Corner<T> c = corners<T>(lane, fx, fy, fz);
+            const Corner<T> c = corners<T>(kLanes ? 0 : lane, fx, fy, fz);
             const unsigned dx = (unsigned)(i0 - ci + 1), dy = (unsigned)(j0 - cj + 1), dz = (unsigned)(k0 - ck + 1);
             if (!single && dx < 2u && dy < 2u && dz < 2u)
               blk_cic<T, 3>(bf + dx + 3 * (dy + 3 * dz), c, q, fits);
@@ -2591,11 +2601,16 @@ static int deposit_and_solve(itokmc_ctx* ctx, FieldState* F, const StepConst& K,
     int g = (int)((ctx->cap + kDepChunk - 1) / kDepChunk);
     g = g < 1 ? 1 : (g > 16384 ? 16384 : g);
     if (ctx->d.shape == ITOKMC_SHAPE_TSC)
-      k_field_deposit_lds<T, 1><<<g, 256, dep_lds_bytes<T, 1>(), s>>>(
+      k_field_deposit_lds<T, 1, false><<<g, 256, dep_lds_bytes<T, 1, false>(), s>>>(
           ctx->bank[ctx->cur], ctx->ctr, ctx->cur, K, Eo, coef(ctx), mode, (S*)F->sig, (S*)F->ne, (T*)ctx->mu_p);
-    else
-      k_field_deposit_lds<T, 0><<<g, 256, dep_lds_bytes<T, 0>(), s>>>(
+    else if (sizeof(T) == 8 || ctx->cap >= kDepFew)
+      k_field_deposit_lds<T, 0, false><<<g, 256, dep_lds_bytes<T, 0, false>(), s>>>(
           ctx->bank[ctx->cur], ctx->ctr, ctx->cur, K, Eo, coef(ctx), mode, (S*)F->sig, (S*)F->ne, (T*)ctx->mu_p);
+    if constexpr (sizeof(T) == 4) {
+      if (ctx->d.shape != ITOKMC_SHAPE_TSC)
+        k_field_deposit_lds<T, 0, true><<<g, 256, dep_lds_bytes<T, 0, true>(), s>>>(
+            ctx->bank[ctx->cur], ctx->ctr, ctx->cur, K, Eo, coef(ctx), mode, (S*)F->sig, (S*)F->ne, (T*)ctx->mu_p);
+    }
   }
   phase_end(ctx, PH_DEPOSIT);
   phase_begin(ctx, PH_FIELD_PREP);

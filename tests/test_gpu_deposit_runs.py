@@ -77,10 +77,10 @@ def test_runs(itk, orc, prec, tol, shape, disp):
 
 @pytest.mark.parametrize("shape", ["cic", "tsc"])
 def test_many_particles_in_any_order(itk, shape):
-    """Past 2^20 particles (CIC's other line): grouped by cell and shuffled, bit for bit."""
+    """Past 2^21 particles (CIC's other line): grouped by cell and shuffled, bit for bit."""
     cfg = _streamer_small(grid=GRID, shape=shape, precision="fp32", n_ppc=0, gmg_rtol=1e-12, gmg_max_cycles=500)
     rng = np.random.default_rng(91)
-    n, nc = (1 << 20) + 4321, int(np.prod(GRID))
+    n, nc = (1 << 21) + 4321, int(np.prod(GRID))
     cells = np.sort(rng.integers(0, nc, n))
     off = rng.random((n, 3))
     w = rng.integers(1, 4, n).astype(np.uint32)
