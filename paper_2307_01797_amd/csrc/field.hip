@@ -414,10 +414,10 @@ template <> struct DepAcc<float> {
 // against 1.31; 6e6 in 3.2e5 0.29 against 0.32, 4.5e7 in 2.2e6 1.86 against 2.15).  The
 // counts are on the device, so both kernels are launched and one returns (3-5 us).
 //
-// The table takes the blocks of at most kDepDense runs (of 2 or
-// 64 instead of 8: 2.92 and 3.25 ms where 8 takes 1.88, 4.5e7 particles).  CIC in single
-// precision: 512 entries (24 KB with the blocks) and 79 VGPRs let six workgroups of a CU
-// overlap their loads; 1024 entries leave four (2.37 ms).  What bounds it is that latency:
+// The table takes the blocks of at most kDepDense runs (of 2 or 64 instead of 8: 2.92 and
+// 3.25 ms where 8 takes 1.88, 4.5e7 particles).  CIC blocks in single precision: 512
+// entries (24 KB with the blocks) and 79 VGPRs let six workgroups of a CU overlap their
+// loads; 1024 entries leave four (2.37 ms).  What bounds it is that latency:
 // the loads, the field gather and the flush of a chunk follow each other.  Before, each
 // lane added its own contributions to a table of 1024 entries (TSC: sums over runs by
 // segmented scans first): CIC 2.15 ms at 4.5e7 particles, 0.40 -> 0.37 ms at 6.3e6; TSC
