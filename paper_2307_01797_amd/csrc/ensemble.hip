@@ -168,14 +168,17 @@ __global__ void __launch_bounds__(256) e_seed_gaussian(Bank b, Counters* ctr, in
 
 // Push with fused NGP binning over the pool.  Particles of released slots are dropped,
 // particles of finished slots stay binned where they are.  A workgroup takes one
-// contiguous chunk of the bank, whose particles mostly share a realization: a wavefront
-// handles the realizations of its 64 particles one after another (nearly always one),
-// with the realization's constants in scalar registers until it changes, and counts its
-// tallies per wavefront.  The wavefronts' last tallies are added up per workgroup, so that
-// a step costs about one atomic per workgroup on the realizations' few tally words: one per
-// wavefront, and one per particle among the appended products, where realizations
+// contiguous chunk of the bank, whose particles mostly share a realization: a wavefront of
+// one realization keeps its constants in scalar registers until it changes; in one of
+// several (boundaries, appended products, realizations of a few particles) every lane reads
+// its own, and only the tallies go realization by realization (the whole push in that way
+// took 84 us where 1024 realizations hold one electron each; now 13).  Tallies are counted
+// per wavefront and realization, and the wavefronts' last ones are added up per workgroup,
+// so that a step costs about one atomic per workgroup on the realizations' few tally words:
+// one per wavefront, and one per particle among the appended products, where realizations
 // alternate, had been the kernel's time (32 realizations, 1.9e6 particles on average:
-// 0.193 -> 0.079 ms).
+// 0.193 -> 0.079 ms).  Eight wavefronts a SIMD in single precision (72 registers without the
+// bound: seven, and 1.0e7 particles take 272 us instead of 240).
 // bid, nblk: this workgroup's index and the number of workgroups taking part.
 struct PushLds {
   uint32_t slot;
@@ -198,8 +201,8 @@ __device__ __forceinline__ void push_phase(Bank a, Counters* ctr, int which,
     L->v[0] = L->v[1] = L->v[2] = 0ull;
   }
   __syncthreads();
-  // the wavefront's current realization, its constants and its tallies (wave-uniform)
-  uint32_t cur = kInvalidCell, state = ITOKMC_SLOT_FREE;
+  // the realizations whose constants and whose tallies the wavefront holds (wave-uniform)
+  uint32_t held = kInvalidCell, cur = kInvalidCell, state = ITOKMC_SLOT_FREE;
   StepConst K{};
   uint32_t map_off = 0;
   T drift[3] = {(T)0, (T)0, (T)0}, diff = (T)0;
@@ -230,19 +233,29 @@ __device__ __forceinline__ void push_phase(Bank a, Counters* ctr, int which,
       if (s < 0) a.w[i] = 0;  // realization released
     }
     uint64_t todo = __ballot(s >= 0);
-    while (todo) {  // one pass per realization in the wavefront
-      const uint32_t su = lane_u32((uint32_t)s, __ffsll((long long)todo) - 1);
-      const bool mine = s == (int)su;
-      const uint64_t m = __ballot(mine);
-      todo &= ~m;
-      if (su != cur) {
-        if (lane == 0) {
-          if (live) atomicAdd(&st[S_LIVE * ms + cur], (unsigned long long)live);
-          if (left) atomicAdd(&st[S_LEFT * ms + cur], (unsigned long long)left);
-          if (outw) atomicAdd(&st[S_OUTW * ms + cur], (unsigned long long)outw);
-        }
-        cur = su;
-        live = left = outw = 0;
+    bool act = false, gone = false;
+    const auto advance = [&](const StepConst& C, const T dr[3], T df, uint32_t off) {
+      act = true;
+      int ci[3];
+      cell_ijk((lblk << kBlkShift) | (g & kBlkMask), C, ci[0], ci[1], ci[2]);  // the local cell
+      const int lim[3] = {C.nx, C.ny, C.nz};
+      gone = !push_uniform<T>(id, C.step, C.key, dr, df, lim, ci, o);
+      if (!gone) {
+        const uint32_t lc =
+            (uint32_t)ci[0] + (uint32_t)C.nx * ((uint32_t)ci[1] + (uint32_t)C.ny * (uint32_t)ci[2]);
+        key = to_global(lc, map, off);
+        a.cell[i] = key;
+        as<T>(a.ox)[i] = o[0];
+        as<T>(a.oy)[i] = o[1];
+        as<T>(a.oz)[i] = o[2];
+      } else {
+        a.w[i] = 0;
+      }
+    };
+    const uint32_t su = todo ? lane_u32((uint32_t)s, __ffsll((long long)todo) - 1) : held;
+    if (__ballot(s == (int)su) == todo) {
+      if (su != held) {
+        held = su;
         const SlotConst& S = sc[su];
         state = uni(S.state);
         K.nx = (int)uni((uint32_t)S.nx); K.ny = (int)uni((uint32_t)S.ny); K.nz = (int)uni((uint32_t)S.nz);
@@ -253,33 +266,43 @@ __device__ __forceinline__ void push_phase(Bank a, Counters* ctr, int which,
         for (int q = 0; q < 3; ++q) drift[q] = (T)S.drift[q];
         diff = (T)S.diff;
       }
-      if (state != ITOKMC_SLOT_ACTIVE) {
-        if (mine) key = g;
-        continue;
+      if (s >= 0) {
+        if (state == ITOKMC_SLOT_ACTIVE) advance(K, drift, diff, map_off);
+        else key = g;
       }
-      bool gone = false;
-      if (mine) {
-        int ci[3];
-        cell_ijk((lblk << kBlkShift) | (g & kBlkMask), K, ci[0], ci[1], ci[2]);  // the local cell
-        const int lim[3] = {K.nx, K.ny, K.nz};
-        gone = !push_uniform<T>(id, K.step, K.key, drift, diff, lim, ci, o);
-        if (!gone) {
-          const uint32_t lc =
-              (uint32_t)ci[0] + (uint32_t)K.nx * ((uint32_t)ci[1] + (uint32_t)K.ny * (uint32_t)ci[2]);
-          key = to_global(lc, map, map_off);
-          a.cell[i] = key;
-          as<T>(a.ox)[i] = o[0];
-          as<T>(a.oy)[i] = o[1];
-          as<T>(a.oz)[i] = o[2];
-        } else {
-          a.w[i] = 0;
+    } else if (s >= 0) {
+      const SlotConst& S = sc[s];
+      if (S.state == ITOKMC_SLOT_ACTIVE) {
+        StepConst C{};
+        C.nx = S.nx; C.ny = S.ny; C.nz = S.nz;
+        C.mdx = S.mdx; C.sdx = S.sdx; C.mdy = S.mdy; C.sdy = S.sdy;
+        C.step = S.step;
+        C.key = S.key;
+        const T dr[3] = {(T)S.drift[0], (T)S.drift[1], (T)S.drift[2]};
+        advance(C, dr, (T)S.diff, S.map_off);
+      } else {
+        key = g;
+      }
+    }
+    const uint64_t am = __ballot(act), gm = __ballot(gone);
+    todo = am;
+    while (todo) {  // one pass per realization in the wavefront
+      const uint32_t sv = lane_u32((uint32_t)s, __ffsll((long long)todo) - 1);
+      const uint64_t m = __ballot(s == (int)sv) & am;
+      todo &= ~m;
+      if (sv != cur) {
+        if (lane == 0) {
+          if (live) atomicAdd(&st[S_LIVE * ms + cur], (unsigned long long)live);
+          if (left) atomicAdd(&st[S_LEFT * ms + cur], (unsigned long long)left);
+          if (outw) atomicAdd(&st[S_OUTW * ms + cur], (unsigned long long)outw);
         }
+        cur = sv;
+        live = left = outw = 0;
       }
       live += (uint64_t)__popcll(m);
-      const uint64_t gm = __ballot(gone);
-      if (gm) {
-        left += (uint64_t)__popcll(gm);
-        outw += wave_sum64_dpp(gone ? (uint64_t)w : 0ull);
+      if (gm & m) {
+        left += (uint64_t)__popcll(gm & m);
+        outw += wave_sum64_dpp(gone && s == (int)sv ? (uint64_t)w : 0ull);
       }
     }
     const uint32_t rank = bin_add(cellacc, key, w);
@@ -307,7 +330,7 @@ __device__ __forceinline__ void push_phase(Bank a, Counters* ctr, int which,
 }
 
 template <typename T>
-__global__ void __launch_bounds__(1024) e_push(Bank a, Counters* ctr, int which,
+__global__ void __launch_bounds__(1024, sizeof(T) == 4 ? 8 : 4) e_push(Bank a, Counters* ctr, int which,
                                               unsigned long long* cellacc, uint32_t* tiles,
                                               const SlotConst* sc,
                                               const int32_t* blk_slot, const uint32_t* blk_local,
