@@ -550,7 +550,24 @@ __global__ void __launch_bounds__(kBlock) k_scatter(Bank a, Bank b, Counters* ct
                                                    const uint32_t* start, uint32_t cap, uint32_t* from) {
   if (ctr->halt) return;
   const uint32_t n = min(ctr->n[which], cap);
-  if (from == nullptr || n <= kGatherMin) {
+  // two particles per thread and pass, all loads in flight together; a dead slot (weight
+  // 0) or a second index past n reads slot 0 and cell 0 instead and stores nothing
+  const uint32_t stride = gridDim.x * blockDim.x * 2u;
+  if (from != nullptr && n > kGatherMin) {
+    for (uint32_t i0 = blockIdx.x * blockDim.x * 2u + threadIdx.x; i0 < n; i0 += stride) {
+      const uint32_t i1 = i0 + blockDim.x;
+      const uint32_t w0 = a.w[i0], w1 = i1 < n ? a.w[i1] : 0u;
+      const uint32_t j0 = w0 ? i0 : 0u, j1 = w1 ? i1 : 0u;
+      const uint32_t c0 = a.cell[j0], c1 = a.cell[j1];
+      const uint32_t r0 = a.rank[j0], r1 = a.rank[j1];
+      const uint32_t s0 = start[w0 ? c0 : 0u], s1 = start[w1 ? c1 : 0u];
+      if (w0) from[s0 + r0] = i0;
+      if (w1) from[s1 + r1] = i1;
+    }
+    return;
+  }
+  // a scatter of at most two passes of the grid: one particle per thread and pass
+  if (n <= stride) {
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
       const uint32_t w = a.w[i];
       if (w == 0) continue;
@@ -560,18 +577,20 @@ __global__ void __launch_bounds__(kBlock) k_scatter(Bank a, Bank b, Counters* ct
     }
     return;
   }
-  // two particles per thread and pass, all loads in flight together; a dead slot (weight
-  // 0) or a second index past n reads slot 0 and cell 0 instead and stores nothing
-  const uint32_t stride = gridDim.x * blockDim.x * 2u;
+  // of more (an ensemble's pool, which launches 2048 workgroups): in pairs as well (2.4e6
+  // particles 34 against 35.5 us, 2.9e7 702 against 750)
   for (uint32_t i0 = blockIdx.x * blockDim.x * 2u + threadIdx.x; i0 < n; i0 += stride) {
     const uint32_t i1 = i0 + blockDim.x;
     const uint32_t w0 = a.w[i0], w1 = i1 < n ? a.w[i1] : 0u;
     const uint32_t j0 = w0 ? i0 : 0u, j1 = w1 ? i1 : 0u;
     const uint32_t c0 = a.cell[j0], c1 = a.cell[j1];
     const uint32_t r0 = a.rank[j0], r1 = a.rank[j1];
+    const T x0 = as<T>(a.ox)[j0], y0 = as<T>(a.oy)[j0], z0 = as<T>(a.oz)[j0];
+    const T x1 = as<T>(a.ox)[j1], y1 = as<T>(a.oy)[j1], z1 = as<T>(a.oz)[j1];
+    const uint64_t d0 = a.id[j0], d1 = a.id[j1];
     const uint32_t s0 = start[w0 ? c0 : 0u], s1 = start[w1 ? c1 : 0u];
-    if (w0) from[s0 + r0] = i0;
-    if (w1) from[s1 + r1] = i1;
+    if (w0) put<T>(b, s0 + r0, c0, x0, y0, z0, w0, d0);
+    if (w1) put<T>(b, s1 + r1, c1, x1, y1, z1, w1, d1);
   }
 }
 
