@@ -1214,7 +1214,10 @@ __global__ void __launch_bounds__(128) k_prolong3(T* u, int nx, int ny, int nz, 
 // domain has coefficient zero and the cell itself as its neighbour, which adds zero).
 // Bound by the latency of a colour (LDS, a chain of six additions, the division, a
 // barrier).  16^3 in double: 33.8 -> 11.4 us per launch; 9x7x11 bottom, 60 sweeps in double:
-// 180 -> 29 us; 11x9x13 bottom, 68 sweeps in single: 44 -> 28.5 us.
+// 180 -> 29 us; 11x9x13 bottom, 68 sweeps in single: 44 -> 28.5 us.  Three cells of a colour
+// per thread have room for their state in single precision only with the neighbours' LDS
+// offsets packed (a cycle of 28x36x240, whose bottom is 7x9x60: 390 us, of 64x64 in one
+// plane 269; four cells unpacked, with spills: 553 and 584).
 constexpr uint32_t kSmallLevel = 4096;
 static_assert(kBottomMaxCells <= (int)kSmallLevel, "the coarsest level runs as a small level");
 
@@ -1275,22 +1278,30 @@ __global__ void __launch_bounds__(1024) k_small_setup(SmallLevels L, const T* ef
 // coarsest level's sweeps.  LDS: the correction, and with fc_out the residual.
 template <typename T, int NR, int MAXT>
 __global__ void __launch_bounds__(MAXT) k_small_level(T* u, const T* f, const T* cf, int nx, int ny, int nz,
-                                                      int sweeps, bool zero_u, const T* uc_in, T* fc_out,
+                                                      int pair, int sweeps, bool zero_u, const T* uc_in, T* fc_out,
                                                       T* uc_out, int cnx, int cny, int cnz) {
   extern __shared__ __align__(16) char smem[];
-  const int n = nx * ny * nz, sy = nx, sz = nx * ny, h = (nx + 1) >> 1, NT = (int)blockDim.x;
+  const int n = nx * ny * nz, sy = nx, sz = nx * ny, NT = (int)blockDim.x;
+  const int wx = pair == 0 ? (nx + 1) >> 1 : nx, wy = pair == 1 ? (ny + 1) >> 1 : ny;
   T* const su = reinterpret_cast<T*>(smem);
   T* const sr = su + n;
   T b[2][NR][6], dg[2][NR], fr[2][NR];
-  int nb[2][NR][6], cell[2][NR];  // cell: -1 past the colour's cells
+  int cell[2][NR];  // -1 past the colour's cells
+  // the six neighbours' cells or, packed, their byte offsets in LDS (below 2^16), two to a
+  // register
+  constexpr bool kPack = NR > 2;
+  uint32_t nb[2][NR][kPack ? 3 : 6];
 #pragma unroll
   for (int q = 0; q < 2; ++q)
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      // the colour's cells row by row: position m of a row's colour q is x = 2 m + parity
-      const int p = (int)threadIdx.x + r * NT, row = p / h, m = p - row * h;
-      const int k = row / ny, j = row - k * ny, i = 2 * m + ((j + k + q) & 1);
-      const bool own = k < nz && i < nx;
+      // the colour's cells row by row: along the axis `pair`, position m is cell 2 m + parity
+      const int p = (int)threadIdx.x + r * NT, row = p / wx;
+      int i = p - row * wx, k = row / wy, j = row - k * wy;
+      if (pair == 0) i = 2 * i + ((j + k + q) & 1);
+      else if (pair == 1) j = 2 * j + ((i + k + q) & 1);
+      else k = 2 * k + ((i + j + q) & 1);
+      const bool own = i < nx && j < ny && k < nz;
       const int c = own ? i + sy * j + sz * k : 0;
       cell[q][r] = own ? c : -1;
       bool in[6];
@@ -1299,7 +1310,10 @@ __global__ void __launch_bounds__(MAXT) k_small_level(T* u, const T* f, const T*
                           in[3] ? sy : 0, in[4] ? -sz : 0, in[5] ? sz : 0};
 #pragma unroll
       for (int a = 0; a < 6; ++a) {
-        nb[q][r][a] = c + off[a];
+        const uint32_t at = (uint32_t)(c + off[a]);
+        if constexpr (!kPack) nb[q][r][a] = at;
+        else if (a & 1) nb[q][r][a >> 1] |= at * (uint32_t)sizeof(T) << 16;
+        else nb[q][r][a >> 1] = at * (uint32_t)sizeof(T);
         // the face below a cell is the + face of its lower neighbour
         const T v = cf[4 * (size_t)((a & 1) ? c : c + off[a]) + (a >> 1)];
         b[q][r][a] = in[a] ? v : (T)0;
@@ -1309,23 +1323,34 @@ __global__ void __launch_bounds__(MAXT) k_small_level(T* u, const T* f, const T*
       T v = zero_u ? (T)0 : u[c];
       if (uc_in && own) v = v + prolong_value<T>(uc_in, cnx, cny, cnz, i, j, k);
       if (own) su[c] = v;
+      if (NR > 2) __builtin_amdgcn_sched_barrier(0);  // the next cell's loads would need spills
     }
   __syncthreads();
-  auto nbsum = [&](int q, int r) {
+  // `zero` is opaque to the compiler, so that the offsets stay packed outside the loop
+  auto nbsum = [&](int q, int r, uint32_t zero) {
     T un[6];
 #pragma unroll
-    for (int a = 0; a < 6; ++a) un[a] = su[nb[q][r][a]];
+    for (int a = 0; a < 6; ++a) {
+      if constexpr (kPack) {
+        const uint32_t w = nb[q][r][a >> 1];
+        un[a] = *reinterpret_cast<const T*>(smem + ((a & 1) ? w >> (16u + zero) : w & (0xFFFFu + zero)));
+      } else {
+        un[a] = su[nb[q][r][a]];
+      }
+    }
     T acc = 0;
 #pragma unroll
     for (int a = 0; a < 6; ++a) acc = acc + b[q][r][a] * un[a];
     return acc;
   };
+  uint32_t zero = 0;
   for (int it = 0; it < sweeps; ++it) {
+    if constexpr (kPack) asm volatile("" : "+s"(zero));
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
-        const T v = smooth_div(fr[q][r] + nbsum(q, r), dg[q][r]);
+        const T v = smooth_div(fr[q][r] + nbsum(q, r, zero), dg[q][r]);
         if (cell[q][r] >= 0) su[cell[q][r]] = v;
       }
       __syncthreads();
@@ -1339,7 +1364,7 @@ __global__ void __launch_bounds__(MAXT) k_small_level(T* u, const T* f, const T*
       if (c < 0) continue;
       const T uc = su[c];
       u[c] = uc;
-      if (fc_out) sr[c] = fr[q][r] - (dg[q][r] * uc - nbsum(q, r));
+      if (fc_out) sr[c] = fr[q][r] - (dg[q][r] * uc - nbsum(q, r, zero));
     }
   if (fc_out) {
     __syncthreads();
@@ -1356,21 +1381,26 @@ __global__ void __launch_bounds__(MAXT) k_small_level(T* u, const T* f, const T*
   }
 }
 
+static int n_pairs(int n, bool paired) { return paired ? (n + 1) / 2 : n; }
 template <typename T>
 static void launch_small_level(hipStream_t s, T* u, const T* f, const T* cf, int nx, int ny, int nz, int sweeps,
                                bool zero_u, const T* uc_in, T* fc_out, T* uc_out, int cnx, int cny, int cnz) {
-  const int pos = ((nx + 1) / 2) * ny * nz;  // positions of one colour (n <= 4096: at most 4096)
-  const int nr = pos <= 1024 ? 1 : pos <= 2048 ? 2 : 4;
+  // positions of one colour: pairs of cells along x, or along the longest axis where rows of
+  // one or three cells would leave a half or a quarter of the positions empty.  n <= 4096
+  // makes at most 2458 of them (rows of five).
+  const int pair = nx != 1 && nx != 3 ? 0 : (ny > nz ? 1 : 2);
+  const int pos = n_pairs(nx, pair == 0) * n_pairs(ny, pair == 1) * n_pairs(nz, pair == 2);
+  const int nr = pos <= 1024 ? 1 : pos <= 2048 ? 2 : 3;
   const int nt = ((pos + nr - 1) / nr + 63) / 64 * 64;
   const size_t lds = (size_t)(fc_out ? 2 : 1) * nx * ny * nz * sizeof(T);
   const auto go = [&](auto kern) {
-    kern<<<1, nt, lds, s>>>(u, f, cf, nx, ny, nz, sweeps, zero_u, uc_in, fc_out, uc_out, cnx, cny, cnz);
+    kern<<<1, nt, lds, s>>>(u, f, cf, nx, ny, nz, pair, sweeps, zero_u, uc_in, fc_out, uc_out, cnx, cny, cnz);
   };
   if (nt == 64) go(k_small_level<T, 1, 64>);
   else if (nr == 1 && nt <= 512) go(k_small_level<T, 1, 512>);
   else if (nr == 1) go(k_small_level<T, 1, 1024>);
   else if (nr == 2) go(k_small_level<T, 2, 1024>);
-  else go(k_small_level<T, 4, 1024>);
+  else go(k_small_level<T, 3, 1024>);
 }
 
 // ---- tiled levels ---------------------------------------------------------------------
