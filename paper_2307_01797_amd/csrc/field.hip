@@ -448,11 +448,12 @@ __device__ __forceinline__ uint32_t tbl_slot(uint32_t x, uint32_t row) {
   return (x + ((row * 2654435761u) >> (32 - L2))) & ((1u << L2) - 1u);
 }
 
-// Add e to the node's sum of one field (v in the table, g in global memory).
+// Add e to the node's sum of one field (v in the table, g in global memory).  The probes are
+// unrolled: nearly every call ends at the first (as a loop 1.6e6 particles of 3 a cell take
+// 193 us instead of 181).
 template <typename S, int L2>
 __device__ __forceinline__ void tbl_put(uint32_t* keys, S* v, uint32_t node, uint32_t h, S e, S* g) {
   if (e == (S)0) return;
-#pragma unroll 1
   for (int probe = 0; probe < kDepProbes; ++probe) {
     uint32_t k = keys[h];
     if (k == kEmptyKey) {
