@@ -41,7 +41,7 @@ HBM_PEAK_GBS = 8000.0
 #                      next counts (write 8), read the counts (8), copy back (read 8,
 #                      write 8): 32; the field and the atomics of ion-holding cells are
 #                      not counted
-KERNELS = {"push": "k_push_uniform", "field_push": "k_push_field", "deposit": "k_field_deposit_lds",
+KERNELS = {"push": "k_push_uniform", "field_push": "k_push_field", "deposit": "k_field_deposit",
            "scatter": "k_scatter", "couple": "k_couple", "smooth_fine": "k_smooth_seg<fine>",
            "ions": "k_ion_move"}
 

@@ -386,59 +386,72 @@ template <> struct DepAcc<float> {
 // reads it instead of interpolating E^k again.
 //
 // A workgroup takes a chunk of kDepChunk consecutive (cell-sorted, hence spatially compact)
-// particles, one per thread, and sums in LDS on two levels.
+// particles, one per thread, and sums them in LDS before the global atomics (25e9 requests of
+// a 64 B line a second, whatever they hold).  Two kernels:
 //
-// * Cell blocks: each run of equal cells in a wavefront, kDepRuns of them at a time, has
-//   the nodes around its cell as a small dense array (CIC and the conductivity 3^3; TSC's
-//   displaced charge 5^3), so that a contribution is one LDS atomic at a fixed offset,
-//   without a node index, a hash or a key, and neighbouring lanes of a run take its nodes
-//   in different orders: 64 lanes that add to one address take 128 cycles, to 8 of them in
-//   turn 15.
-// * Table: the blocks of a wavefront of at most kDepDense runs (cells of 8 particles and
-//   more) are added, one node per lane, to a hash table keyed by grid node (linear probing,
-//   at most kDepProbes probes, then a direct global atomic), flushed with one global atomic
-//   per touched node and field: consecutive cells share most of their nodes.  The blocks of
-//   a wavefront of more runs would fill the table with nodes that hardly repeat, so they go
-//   to the grid directly, a node per lane: a row of a block is one request of the global
-//   atomics (25e9 lines of 64 B a second, whatever they hold), where a particle by itself
-//   is one request per node.
-// * A particle displaced out of its block adds to the table by itself.  So does, with CIC in
-//   double precision, one of a wavefront of more than kDepRuns runs (64^3, 4e5 particles:
-//   104 against 93 us).
+// * k_field_deposit_lanes: every particle adds to a hash table keyed by grid node (linear
+//   probing, at most kDepProbes probes, then a direct global atomic), flushed with one
+//   global atomic per touched node and field: consecutive cells share most of their nodes.
+//   TSC in single precision first sums over runs of equal cells (tbl_tsc_runs).
+// * k_field_deposit_blocks: each run of equal cells in a wavefront, kDepRuns of them at a
+//   time, has the nodes around its cell as a small dense array (CIC and the conductivity
+//   3^3; TSC's displaced charge 5^3), so that a contribution is one LDS atomic at a fixed
+//   offset, without a hash or a key, and neighbouring lanes of a run take its nodes in
+//   different orders (64 lanes that add to one address take 128 cycles, to 8 of them in turn
+//   15).  The blocks of a wavefront of at most kDepDense runs go to the table, one node per
+//   lane; those of more would fill it with nodes that hardly repeat, so they go to the grid,
+//   a row of a block being one request.  A particle displaced out of its block adds to the
+//   table by itself; so does, with CIC in double precision, one of a wavefront of more than
+//   kDepRuns runs.
 //
-// kLanes (CIC in single precision): every particle adds to a table of 1024 entries by
-// itself, without blocks.  It takes launches of fewer than kDepFew particles, which are as
-// long as one wavefront (128^3 request 34 against 29 us), and those of fewer than kDepFull
-// particles per occupied cell, where the wavefronts of many runs would go through batches of
-// blocks after each other (1.0e7 particles in 3.3e6 cells 1.12 ms against 0.97, 1.3e7 1.72
-// against 1.31; 6e6 in 3.2e5 0.29 against 0.32, 4.5e7 in 2.2e6 1.86 against 2.15).  The
-// counts are on the device, so both kernels are launched and one returns (3-5 us).
+// Blocks win where cells hold many particles, lanes where a wavefront's many runs would go
+// through batches of blocks after each other.  The lines (dep_lanes), in particles and in
+// particles per occupied cell; ms of lanes | blocks:
+//   CIC, single: 2^21 particles (a launch of fewer is as long as one wavefront: 128^3 request
+//     0.029 | 0.034) and 12 a cell (1.0e7 in 3.3e6 cells 0.97 | 1.12, 1.3e7 1.31 | 1.72; 6e6
+//     in 3.2e5 0.32 | 0.29, 4.5e7 in 2.2e6 2.15 | 1.86).
+//   CIC, double: 5 a cell from 2^19 particles on (1.6e6 in adjacent cells, 3 a cell 0.200 |
+//     0.239, 6 a cell 0.161 | 0.172, 16 a cell 0.137 | 0.112; 2e5 of 2 a cell 0.067 | 0.058).
+//   TSC, single: 5 a cell (1.6e6 in adjacent cells, 1 a cell 0.44 | 1.72, 4 a cell 0.31 |
+//     0.43, 6 a cell 0.31 | 0.32, 8 a cell 0.270 | 0.271; streamers of 4.8 a cell 0.66 | 0.70,
+//     of 5.2 2.73 | 1.91), below 2^19 particles 3 (2e4 of 2 a cell 0.062 | 0.065, of 4 0.056 |
+//     0.036).
+//   TSC, double: 2 a cell (1.6e6, 1 a cell 1.03 to 1.35 | 2.0 to 2.1, 2 a cell 1.00 to 1.67 |
+//     1.11 to 1.16).
+// The counts are on the device, so both kernels are launched and one returns (2-10 us: a
+// workgroup's LDS is allocated all the same).
 //
-// The table takes the blocks of at most kDepDense runs (of 2 or 64 instead of 8: 2.92 and
+// The table takes the blocks of at most kDepDense runs (CIC: of 2 or 64 instead of 8 2.92 and
 // 3.25 ms where 8 takes 1.88, 4.5e7 particles).  CIC blocks in single precision: 512
 // entries (24 KB with the blocks) and 79 VGPRs let six workgroups of a CU overlap their
-// loads; 1024 entries leave four (2.37 ms).  What bounds it is that latency:
-// the loads, the field gather and the flush of a chunk follow each other.  Before, each
-// lane added its own contributions to a table of 1024 entries (TSC: sums over runs by
-// segmented scans first): CIC 2.15 ms at 4.5e7 particles, 0.40 -> 0.37 ms at 6.3e6; TSC
-// 1.45 -> 0.74 ms at 3.7e6 (the same table, overfull with the nodes of single particles,
-// and 2.5e7 -> 1.3e7 global requests at the end of a run).  Double precision 96 -> 93 us
-// at 4e5 particles.
+// loads; 1024 entries leave four (2.37 ms).  What bounds it is that latency: the loads, the
+// field gather and the flush of a chunk follow each other.
 constexpr int kDepChunk = 256;
 constexpr int kDepProbes = 8;
 template <int SH> constexpr int kDepRuns = SH == 0 ? 8 : 4;  // 4: 2.01 ms, 16: 2.21 (CIC)
 constexpr int kDepDense = 8;
-constexpr uint32_t kDepFew = 1u << 21;
+template <typename T> constexpr uint32_t kDepFew = sizeof(T) == 4 ? 1u << 21 : 1u << 19;  // CIC
 constexpr uint32_t kEmptyKey = 0xFFFFFFFFu;
-template <typename T, int SH, bool kLanes> constexpr int kDepL2 = SH == 0 && sizeof(T) == 4 && !kLanes ? 9 : 10;
-constexpr uint32_t kDepFull = 12;
+template <typename T, int SH> constexpr int kDepL2 = SH == 0 && sizeof(T) == 4 ? 9 : 10;  // the blocks' table
+constexpr int kDepLanesL2 = 10;
 // Nodes per axis of a run's block of the displaced charge.
 template <int SH> constexpr int kDepW = SH == 0 ? 3 : 5;
 template <int SH> constexpr int kDepBlock = 27 + kDepW<SH> * kDepW<SH> * kDepW<SH>;
-template <typename T, int SH, bool kLanes>
-constexpr size_t dep_lds_bytes() {
-  return ((size_t)1 << kDepL2<T, SH, kLanes>) * (4 + 2 * sizeof(typename DepAcc<T>::S)) +
-         (kLanes ? (size_t)0 : (size_t)(kDepChunk / 64) * kDepRuns<SH> * kDepBlock<SH> * sizeof(typename DepAcc<T>::S));
+template <typename T, int SH>
+constexpr size_t dep_lds_bytes(bool lanes) {
+  using S = typename DepAcc<T>::S;
+  return lanes ? ((size_t)1 << kDepLanesL2) * (4 + 2 * sizeof(S))
+               : ((size_t)1 << kDepL2<T, SH>) * (4 + 2 * sizeof(S)) +
+                     (size_t)(kDepChunk / 64) * kDepRuns<SH> * kDepBlock<SH> * sizeof(S);
+}
+
+// True if the particles are left to the per-lane kernel (see above for the lines).
+template <typename T, int SH>
+__device__ __forceinline__ bool dep_lanes(uint32_t n, const Counters* ctr) {
+  const uint32_t occ = ctr->n_occ;
+  if constexpr (SH == 0 && sizeof(T) == 4) return n < kDepFew<T> || n / 12u < occ;
+  else if constexpr (SH == 0) return n >= kDepFew<T> && n / 5u < occ;
+  else return n / (sizeof(T) == 8 ? 2u : n < (1u << 19) ? 3u : 5u) < occ;
 }
 
 // Slot of a node in the table: the row hashed, x kept in order, so that a row's nodes sit
@@ -512,11 +525,11 @@ __device__ __forceinline__ void tbl_cic(uint32_t* keys, typename DepAcc<T>::S* v
 }
 
 // The 27 TSC contributions of one particle (clamped wall nodes repeat and simply add).
-template <typename T, int L2>
+template <typename T, int L2, int U>
 __device__ __forceinline__ void tbl_tsc(uint32_t* keys, typename DepAcc<T>::S* v, const StepConst& K,
                                         const Tsc<T>& s, double q, bool fits, typename DepAcc<T>::S* g) {
   using S = typename DepAcc<T>::S;
-#pragma unroll 1
+#pragma unroll U
   for (int cb = 0; cb < 9; ++cb) {
     const int c = cb / 3, b = cb - 3 * c;
     const T wy = b == 0 ? s.wy[0] : b == 1 ? s.wy[1] : s.wy[2], wz = c == 0 ? s.wz[0] : c == 1 ? s.wz[1] : s.wz[2];
@@ -569,25 +582,187 @@ __device__ __forceinline__ void blk_tsc(typename DepAcc<T>::S* blk, int W, int l
       }
 }
 
-template <typename T, int SH, bool kLanes>
-__global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? (kLanes ? 7 : 6) : 4) : (SH == 0 ? 4 : 1))
-    k_field_deposit_lds(Bank a, const Counters* ctr, int which, StepConst K, const void* E4, Coef co, int mode,
-                        typename DepAcc<T>::S* sig, typename DepAcc<T>::S* ne, T* mu_out) {
+// The 27 contributions in single precision, one particle per lane of a whole wavefront
+// (inactive lanes contribute nothing): particles of one cell (before the walls' clamping)
+// share their nodes, so each node's fixed-point contributions are summed over every run of
+// equal cells j by a segmented scan and the run's last lane inserts the sum.
+template <int L2>
+__device__ __forceinline__ void tbl_tsc_runs(uint32_t* keys, unsigned long long* v, const StepConst& K,
+                                             const Tsc<float>& s, bool active, int jx, int jy, int jz, double q,
+                                             bool fits, unsigned long long* g) {
+  const int lane = lane_id();
+  // run key: the three cell indices, each biased into 21 bits (an index off the grid by
+  // up to 2^20 cells still has a key of its own); inactive lanes all differ from it
+  const uint64_t key = active ? ((uint64_t)(uint32_t)(jx + (1 << 20)) << 42) |
+                                    ((uint64_t)(uint32_t)(jy + (1 << 20)) << 21) |
+                                    (uint64_t)(uint32_t)(jz + (1 << 20))
+                              : ~0ull;
+  const uint32_t klo = (uint32_t)key, khi = (uint32_t)(key >> 32);
+  const uint32_t plo = dpp_from_prev(klo, ~klo), phi = dpp_from_prev(khi, ~khi);
+  const uint32_t nlo = dpp_from_next(klo, ~klo), nhi = dpp_from_next(khi, ~khi);
+  const uint32_t head = (plo != klo || phi != khi) ? 1u : 0u;
+  const bool tail = active && (lane == 63 || nlo != klo || nhi != khi);
+  // no run of two or more in the wavefront: every lane inserts its own contributions
+  const bool runs = __ballot(active && lane > 0 && head == 0u) != 0ull;
+  const uint64_t zid[1] = {0ull};
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      const uint32_t row = (uint32_t)s.iy[b] + (uint32_t)K.ny * (uint32_t)s.iz[c];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const float wt = (s.wx[a] * s.wy[b]) * s.wz[c];
+        uint64_t e[1] = {active ? DepAcc<float>::enc(q * (double)wt, fits) : 0ull};
+        if (runs) (void)seg_scan(e, head, zid, [](int, uint64_t u, uint64_t w) { return u + w; });
+        if (tail)
+          tbl_put<unsigned long long, L2>(keys, v, (uint32_t)s.ix[a] + (uint32_t)K.nx * row,
+                                          tbl_slot<L2>((uint32_t)s.ix[a], row), e[0], g);
+      }
+    }
+  }
+}
+
+// The table's flush: one global atomic per touched node and field; the table is left empty.
+template <typename S, int TBL>
+__device__ __forceinline__ void tbl_flush(uint32_t* keys, S* v0, S* v1, S* g0, S* g1) {
+  for (int t = threadIdx.x; t < TBL; t += kDepChunk) {
+    const uint32_t k = keys[t];
+    if (k == kEmptyKey) continue;
+    const S e0 = v0[t], e1 = v1[t];
+    if (e0 != (S)0) atomicAdd(&g0[k], e0);
+    if (e1 != (S)0) atomicAdd(&g1[k], e1);
+    keys[t] = kEmptyKey;
+    v0[t] = (S)0;
+    v1[t] = (S)0;
+  }
+}
+
+template <typename T, int SH>
+__global__ void __launch_bounds__(256, sizeof(T) == 4 && SH == 0 ? 7 : 1)
+    k_field_deposit_lanes(Bank a, const Counters* ctr, int which, StepConst K, const void* E4, Coef co, int mode,
+                          typename DepAcc<T>::S* sig, typename DepAcc<T>::S* ne, T* mu_out) {
   using A = DepAcc<T>;
   using S = typename A::S;
-  constexpr int L2 = kDepL2<T, SH, kLanes>, TBL = 1 << L2, W = kDepW<SH>, B = kDepBlock<SH>;
+  constexpr int L2 = kDepLanesL2, TBL = 1 << L2;
+  extern __shared__ __align__(16) char smem[];
+  S* v0 = reinterpret_cast<S*>(smem);
+  S* v1 = v0 + TBL;
+  uint32_t* keys = reinterpret_cast<uint32_t*>(v1 + TBL);
+  const uint32_t n = min(ctr->n[which], K.cap);
+  if (!dep_lanes<T, SH>(n, ctr)) return;
+  const T diff = (T)K.diff;
+  for (int t = threadIdx.x; t < TBL; t += kDepChunk) {
+    keys[t] = kEmptyKey;
+    v0[t] = (S)0;
+    v1[t] = (S)0;
+  }
+  __syncthreads();
+  for (uint32_t c0 = blockIdx.x * kDepChunk; c0 < n; c0 += gridDim.x * kDepChunk) {
+    const uint32_t i = c0 + threadIdx.x;
+    const uint32_t w = i < n ? a.w[i] : 0u;
+    if constexpr (SH == 1 && sizeof(T) == 4) {
+      // every lane takes part in the run sums (inactive: weight 0)
+      const bool act = w != 0u;
+      Tsc<T> sk{}, sd{};
+      int jk[3] = {0, 0, 0}, jd[3] = {0, 0, 0};
+      double qs = 0.0;
+      const double qn = (double)w * A::kUnit[1];
+      if (act) {
+        cell_ijk(a.cell[i], K, jk[0], jk[1], jk[2]);
+        const T o[3] = {tp<T>(a.ox)[i], tp<T>(a.oy)[i], tp<T>(a.oz)[i]};
+        sk = tsc_at<T>(K, jk[0], jk[1], jk[2], o[0], o[1], o[2]);
+        if (mode != 0) {
+          T e[3];
+          tsc_get3<T>(ctp<T>(E4), K, sk, e);
+          const T mu = Mob<T>::mu(co, sqrt(e[0] * e[0] + e[1] * e[1] + e[2] * e[2]));
+          mu_out[i] = mu;
+          qs = (double)mu * (double)w * A::kUnit[0];
+          const uint64_t id = a.id[i];
+          const uint4 r = philox_block((uint32_t)id, (uint32_t)(id >> 32), K.step, TAG_PUSH, 0, K.key);
+          T nr[3];
+          NormalsF<T>::get(r, nr);
+          const T t[3] = {o[0] + diff * nr[0], o[1] + diff * nr[1], o[2] + diff * nr[2]};
+          sd = tsc_at<T>(K, jk[0], jk[1], jk[2], t[0], t[1], t[2]);
+#pragma unroll
+          for (int q = 0; q < 3; ++q) jd[q] = jk[q] + (int)floor(t[q]);
+        }
+      }
+      const bool fits = __ballot(!(qs < 0x1p52 && qn < 0x1p52)) == 0ull;
+      if (mode == 0) {
+        tbl_tsc_runs<L2>(keys, v1, K, sk, act, jk[0], jk[1], jk[2], qn, fits, ne);
+      } else {
+        tbl_tsc_runs<L2>(keys, v0, K, sk, act, jk[0], jk[1], jk[2], qs, fits, sig);
+        tbl_tsc_runs<L2>(keys, v1, K, sd, act, jd[0], jd[1], jd[2], qn, fits, ne);
+      }
+    } else if (w) {
+      const uint32_t cell = a.cell[i];
+      int ci, cj, ck;
+      cell_ijk(cell, K, ci, cj, ck);
+      const T o[3] = {tp<T>(a.ox)[i], tp<T>(a.oy)[i], tp<T>(a.oz)[i]};
+      const double qn = (double)w * A::kUnit[1];
+      // the charge at the particle's position (conductivity, or electrons of the first field)
+      // and, in a step, the electrons at its displaced one
+      const auto add = [&](const T t[3], double q, S* v, S* g) {
+        const bool fits = __ballot(!(q < 0x1p52)) == 0ull;
+        if constexpr (SH == 0) {
+          int i0, j0, k0;
+          T fx, fy, fz;
+          tent_axis<T>(ci, t[0], K.nx, i0, fx);
+          tent_axis<T>(cj, t[1], K.ny, j0, fy);
+          tent_axis<T>(ck, t[2], K.nz, k0, fz);
+          tbl_cic<T, L2>(keys, v, K, i0, j0, k0, corners<T>(0, fx, fy, fz), q, fits, g);
+        } else {
+          tbl_tsc<T, L2, 9>(keys, v, K, tsc_at<T>(K, ci, cj, ck, t[0], t[1], t[2]), q, fits, g);
+        }
+      };
+      if (mode == 0) {
+        add(o, qn, v1, ne);
+      } else {
+        T e[3];
+        if constexpr (SH == 0) {
+          int i0, j0, k0;
+          T fx, fy, fz;
+          tent_axis<T>(ci, o[0], K.nx, i0, fx);
+          tent_axis<T>(cj, o[1], K.ny, j0, fy);
+          tent_axis<T>(ck, o[2], K.nz, k0, fz);
+          cic_get3<T>(ctp<T>(E4), K, i0, j0, k0, fx, fy, fz, e);
+        } else {
+          tsc_get3<T>(ctp<T>(E4), K, tsc_at<T>(K, ci, cj, ck, o[0], o[1], o[2]), e);
+        }
+        const T mu = Mob<T>::mu(co, sqrt(e[0] * e[0] + e[1] * e[1] + e[2] * e[2]));
+        mu_out[i] = mu;
+        add(o, (double)mu * (double)w * A::kUnit[0], v0, sig);
+        const uint64_t id = a.id[i];
+        const uint4 r = philox_block((uint32_t)id, (uint32_t)(id >> 32), K.step, TAG_PUSH, 0, K.key);
+        T nr[3];
+        NormalsF<T>::get(r, nr);
+        const T t[3] = {o[0] + diff * nr[0], o[1] + diff * nr[1], o[2] + diff * nr[2]};
+        add(t, qn, v1, ne);
+      }
+    }
+    __syncthreads();
+    tbl_flush<S, TBL>(keys, v0, v1, sig, ne);
+    __syncthreads();
+  }
+}
+
+template <typename T, int SH>
+__global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? 6 : 4) : (SH == 0 ? 4 : 1))
+    k_field_deposit_blocks(Bank a, const Counters* ctr, int which, StepConst K, const void* E4, Coef co, int mode,
+                           typename DepAcc<T>::S* sig, typename DepAcc<T>::S* ne, T* mu_out) {
+  using A = DepAcc<T>;
+  using S = typename A::S;
+  constexpr int L2 = kDepL2<T, SH>, TBL = 1 << L2, W = kDepW<SH>, B = kDepBlock<SH>;
   extern __shared__ __align__(16) char smem[];
   __shared__ uint32_t rcell[kDepChunk / 64][kDepRuns<SH>];
   S* v0 = reinterpret_cast<S*>(smem);
   S* v1 = v0 + TBL;
   const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   S* const blocks = v1 + TBL + (size_t)wv * kDepRuns<SH> * B;  // this wavefront's
-  uint32_t* keys = reinterpret_cast<uint32_t*>(v1 + TBL + (kLanes ? 0 : (kDepChunk / 64) * kDepRuns<SH> * B));
+  uint32_t* keys = reinterpret_cast<uint32_t*>(v1 + TBL + (kDepChunk / 64) * kDepRuns<SH> * B);
   const uint32_t n = min(ctr->n[which], K.cap);
-  if constexpr (SH == 0 && sizeof(T) == 4) {
-    const bool lanes = n < kDepFew || n / kDepFull < ctr->n_occ;
-    if (lanes != kLanes) return;
-  }
+  if (dep_lanes<T, SH>(n, ctr)) return;
   const T diff = (T)K.diff;
   for (int t = threadIdx.x; t < TBL; t += kDepChunk) {
     keys[t] = kEmptyKey;
@@ -638,7 +813,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? (kLanes ? 7 :
     const double qn = (double)w * A::kUnit[1];
     // contributions small enough for the short conversion, in every lane of the wavefront
     const bool fits = __ballot(!(qs < 0x1p52 && qn < 0x1p52)) == 0ull;
-    const bool single = kLanes || (SH == 0 && sizeof(T) == 8 && runs > kDepRuns<SH>);  // wave-uniform
+    const bool single = SH == 0 && sizeof(T) == 8 && runs > kDepRuns<SH>;  // wave-uniform
 #pragma unroll 1
     for (int r0 = 0; r0 < runs; r0 += single ? 64 : kDepRuns<SH>) {
       const int nr = single ? 0 : min(runs - r0, kDepRuns<SH>);
@@ -658,7 +833,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? (kLanes ? 7 :
             tent_axis<T>(ci, t[0], K.nx, i0, fx);
             tent_axis<T>(cj, t[1], K.ny, j0, fy);
             tent_axis<T>(ck, t[2], K.nz, k0, fz);
-            const Corner<T> c = corners<T>(kLanes ? 0 : lane, fx, fy, fz);
+            const Corner<T> c = corners<T>(lane, fx, fy, fz);
             const unsigned dx = (unsigned)(i0 - ci + 1), dy = (unsigned)(j0 - cj + 1), dz = (unsigned)(k0 - ck + 1);
             if (!single && dx < 2u && dy < 2u && dz < 2u)
               blk_cic<T, 3>(bf + dx + 3 * (dy + 3 * dz), c, q, fits);
@@ -672,7 +847,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? (kLanes ? 7 :
             if (fabs(bx) <= reach && fabs(by) <= reach && fabs(bz) <= reach)
               blk_tsc<T>(bf + ((int)bx + f) + wf * (((int)by + f) + wf * ((int)bz + f)), wf, lane, s, q, fits);
             else
-              tbl_tsc<T, L2>(keys, f ? v1 : v0, K, s, q, fits, f ? ne : sig);
+              tbl_tsc<T, L2, 1>(keys, f ? v1 : v0, K, s, q, fits, f ? ne : sig);
           }
         }
       }
@@ -711,16 +886,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? (kLanes ? 7 :
       wave_lds_sync();
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < TBL; t += kDepChunk) {
-      const uint32_t k = keys[t];
-      if (k == kEmptyKey) continue;
-      const S e0 = v0[t], e1 = v1[t];
-      if (e0 != (S)0) atomicAdd(&sig[k], e0);
-      if (e1 != (S)0) atomicAdd(&ne[k], e1);
-      keys[t] = kEmptyKey;
-      v0[t] = (S)0;
-      v1[t] = (S)0;
-    }
+    tbl_flush<S, TBL>(keys, v0, v1, sig, ne);
     __syncthreads();
   }
 }
@@ -2631,16 +2797,20 @@ static int deposit_and_solve(itokmc_ctx* ctx, FieldState* F, const StepConst& K,
   {
     int g = (int)((ctx->cap + kDepChunk - 1) / kDepChunk);
     g = g < 1 ? 1 : (g > 16384 ? 16384 : g);
-    if (ctx->d.shape == ITOKMC_SHAPE_TSC)
-      k_field_deposit_lds<T, 1, false><<<g, 256, dep_lds_bytes<T, 1, false>(), s>>>(
-          ctx->bank[ctx->cur], ctx->ctr, ctx->cur, K, Eo, coef(ctx), mode, (S*)F->sig, (S*)F->ne, (T*)ctx->mu_p);
-    else if (sizeof(T) == 8 || ctx->cap >= kDepFew)
-      k_field_deposit_lds<T, 0, false><<<g, 256, dep_lds_bytes<T, 0, false>(), s>>>(
-          ctx->bank[ctx->cur], ctx->ctr, ctx->cur, K, Eo, coef(ctx), mode, (S*)F->sig, (S*)F->ne, (T*)ctx->mu_p);
-    if constexpr (sizeof(T) == 4) {
-      if (ctx->d.shape != ITOKMC_SHAPE_TSC)
-        k_field_deposit_lds<T, 0, true><<<g, 256, dep_lds_bytes<T, 0, true>(), s>>>(
-            ctx->bank[ctx->cur], ctx->ctr, ctx->cur, K, Eo, coef(ctx), mode, (S*)F->sig, (S*)F->ne, (T*)ctx->mu_p);
+    const auto launch = [&](auto kern, int grid, size_t lds) {
+      kern<<<grid, 256, lds, s>>>(ctx->bank[ctx->cur], ctx->ctr, ctx->cur, K, Eo, coef(ctx), mode, (S*)F->sig,
+                               (S*)F->ne, (T*)ctx->mu_p);
+    };
+    const bool many = ctx->cap >= kDepFew<T>;
+    // a kernel that returns costs its workgroups: 4096 are enough for the per-lane form where
+    // cells hold few particles
+    const int gl = std::min(g, 4096);
+    if (ctx->d.shape == ITOKMC_SHAPE_TSC) {
+      launch(k_field_deposit_blocks<T, 1>, g, dep_lds_bytes<T, 1>(false));
+      launch(k_field_deposit_lanes<T, 1>, gl, dep_lds_bytes<T, 1>(true));
+    } else {
+      if (sizeof(T) == 8 || many) launch(k_field_deposit_blocks<T, 0>, g, dep_lds_bytes<T, 0>(false));
+      if (sizeof(T) == 4 || many) launch(k_field_deposit_lanes<T, 0>, sizeof(T) == 4 ? g : gl, dep_lds_bytes<T, 0>(true));
     }
   }
   phase_end(ctx, PH_DEPOSIT);
