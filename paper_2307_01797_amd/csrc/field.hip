@@ -422,14 +422,15 @@ template <> struct DepAcc<float> {
 // workgroup's LDS is allocated all the same).
 //
 // The table takes the blocks of at most kDepDense runs (CIC: of 2 or 64 instead of 8 2.92 and
-// 3.25 ms where 8 takes 1.88, 4.5e7 particles).  CIC blocks in single precision: 512
+// 3.25 ms where 8 takes 1.88, 4.5e7 particles), with TSC in double precision none (1.6e6 of 8 a
+// cell 0.46 ms, 0.80 with 8; a streamer's 2.8e6 1.28 and 1.39).  CIC blocks in single precision: 512
 // entries (24 KB with the blocks) and 79 VGPRs let six workgroups of a CU overlap their
 // loads; 1024 entries leave four (2.37 ms).  What bounds it is that latency: the loads, the
 // field gather and the flush of a chunk follow each other.
 constexpr int kDepChunk = 256;
 constexpr int kDepProbes = 8;
 template <int SH> constexpr int kDepRuns = SH == 0 ? 8 : 4;  // 4: 2.01 ms, 16: 2.21 (CIC)
-constexpr int kDepDense = 8;
+template <typename T, int SH> constexpr int kDepDense = SH == 1 && sizeof(T) == 8 ? 0 : 8;
 template <typename T> constexpr uint32_t kDepFew = sizeof(T) == 4 ? 1u << 21 : 1u << 19;  // CIC
 constexpr uint32_t kEmptyKey = 0xFFFFFFFFu;
 template <typename T, int SH> constexpr int kDepL2 = SH == 0 && sizeof(T) == 4 ? 9 : 10;  // the blocks' table
@@ -781,7 +782,7 @@ __global__ void __launch_bounds__(256, sizeof(T) == 4 ? (SH == 0 ? 6 : 4) : (SH 
     const uint32_t prev = dpp_from_prev(cell, ~cell);  // lane 0: not its cell
     const uint64_t heads = __ballot(act && prev != cell);
     const int runs = __popcll(heads);
-    const bool dense = runs <= kDepDense;  // wave-uniform
+    const bool dense = runs <= kDepDense<T, SH>;  // wave-uniform
     const uint64_t upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1ull);
     const int run = __popcll(heads & upto) - 1;
     int ci = 0, cj = 0, ck = 0;
