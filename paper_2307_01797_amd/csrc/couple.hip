@@ -210,10 +210,11 @@ hipError_t launch_couple(itokmc_ctx* ctx, const StepConst& k) {
   // every dense cell is queued: 131072 wavefronts, 8 cells of the grid each, even out the
   // cells' costs (0.81 -> 0.76 ms per launch at 6e6 particles, 6.58 -> 6.28 ms at 4.5e7
   // against 32768); a grid of up to 2^18 cells keeps up to 32768 (0.163 ms at 64^3, 4e5
-  // particles; 8192: 0.187).  Without merging only large cells that lose particles come
+  // particles; 8192: 0.187), and so does a bank of up to 2^20 particles, of which few cells
+  // can be dense (1e4 in 256^3: a step 101 -> 85 us, the rest being empty workgroups).  Without merging only large cells that lose particles come
   // here and the launch is mostly empty: 4096 (32^3: 8.4 -> 4.2 us).
   const uint32_t nc = ctx->ncell;
-  const int g = (int)std::max(1u, ctx->d.n_ppc > 0 ? std::min({nc, std::max(32768u, nc / 8u), 131072u})
+  const int g = (int)std::max(1u, ctx->d.n_ppc > 0 ? std::min({nc, std::max(32768u, std::min(nc / 8u, (uint32_t)ctx->cap / 32u)), 131072u})
                                                    : std::min(nc, 4096u));
   const int nl = merge_leaves(ctx->d.n_ppc);
   auto wave = [&](auto tt, auto nlt) {
