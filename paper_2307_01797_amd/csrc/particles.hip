@@ -542,7 +542,11 @@ __global__ void __launch_bounds__(kBlock) k_scan_down(const unsigned long long* 
 // At 5.2e7 particles (7e6 cells) the scatter took 1.73 ms, the two passes take 0.28 + 1.05
 // (2.4 TB/s of the 60 bytes), and 11.9 against 1.8 + 6.6 ms on an unsorted seed; at 4.5e7
 // near the particle cap 2.40 against 0.44 + 1.32 ms; at 8e6 particles 0.147 against 0.045 +
-// 0.110 ms, so the line is drawn between them.  The count is known on the device only.
+// 0.110 ms, so the line is drawn between them (1.8e7, 3e7 and 5e7 particles, start to end of
+// the sort's last part: single precision 0.52, 0.87, 1.65 -> 0.43, 0.74, 1.34 ms, double 0.70,
+// 1.21, 2.40 -> 0.51, 0.94, 1.67).  The count is known on the device only: below the line the
+// second kernel returns (8 us; with fewer workgroups than the scatter's it takes 3 but the
+// gather of 1.8e7 8% more).
 constexpr uint32_t kGatherMin = 1u << 24;
 
 template <typename T>
