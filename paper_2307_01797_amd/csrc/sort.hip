@@ -18,7 +18,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "device.hpp"
 #include "itk.hpp"
@@ -211,14 +213,21 @@ __global__ void __launch_bounds__(kSortBlock) k_sort_scatter(const uint32_t* cel
 // launch latency (2-5 us each for a few hundred KB of traffic); one workgroup is bound by
 // the latency of its phases and what one CU can load and store.  3001 particles, 32768
 // cells, double: 25.0 -> 12.1 us a call in a stream of calls, 30.1 -> 24.8 us waited for.
-// The lines: waited for, 6000 particles 28.5 against 30.2 us, 8192 (eight a thread) 31.3
-// against 29.7; the counters of 36864 cells are what LDS holds.
-constexpr int kSortOnePer = 6;  // particles per thread
+//
+// Up to 3072 particles go straight to their slots.  In any order that costs what the six
+// launches do at most (3001 in random order 18.4 us, 29.8 waited for); of more, random
+// slots are a line for every store and one CU (6144 25.9 us, 41.2 waited for).  So the arrays
+// of up to 6144 go through LDS one after another, which takes 1 us more of nearly sorted
+// particles (6144 17.6 us, 28.9 waited for) and the same of random ones (18.0 and 29.3).  The
+// lines: 8192 particles waited for 31.3 against 29.7 us, and the counters of 36864 cells are
+// what LDS holds.
+constexpr int kSortOnePer = 6;  // particles per thread (3 if they go straight)
 constexpr uint32_t kSortOneN = 1024 * kSortOnePer;
+constexpr uint32_t kSortOneStraight = kSortOneN / 2;
 constexpr uint32_t kSortOneCells = 36 << 10;
 __host__ __device__ constexpr uint32_t sort_one_word(uint32_t c) { return c + (c >> 5); }
 
-template <typename T>
+template <typename T, bool kStraight>
 __global__ void __launch_bounds__(1024) k_sort_one(const uint32_t* cell, const T* ox, const T* oy, const T* oz,
                                                    const uint32_t* w, const uint64_t* id, uint32_t n,
                                                    uint32_t ncell, uint32_t* cell_o, T* ox_o, T* oy_o,
@@ -226,10 +235,11 @@ __global__ void __launch_bounds__(1024) k_sort_one(const uint32_t* cell, const T
                                                    uint32_t* n_out) {
   extern __shared__ __align__(16) uint32_t cnt[];
   __shared__ uint32_t sh[1024 / 64];
+  constexpr int kPer = kStraight ? kSortOnePer / 2 : kSortOnePer;
   const uint32_t tid = threadIdx.x;
-  uint32_t key[kSortOnePer], wi[kSortOnePer], rank[kSortOnePer];
+  uint32_t key[kPer], wi[kPer], rank[kPer];
 #pragma unroll
-  for (int q = 0; q < kSortOnePer; ++q) {
+  for (int q = 0; q < kPer; ++q) {
     const uint32_t i = tid + 1024u * q;
     wi[q] = i < n ? w[i] : 0u;
     key[q] = i < n ? cell[i] : kInvalidCell;
@@ -238,7 +248,7 @@ __global__ void __launch_bounds__(1024) k_sort_one(const uint32_t* cell, const T
     reinterpret_cast<uint4*>(cnt)[t] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < kSortOnePer; ++q) {
+  for (int q = 0; q < kPer; ++q) {
     if (wi[q] == 0u || key[q] >= ncell) key[q] = kInvalidCell;
     rank[q] = key[q] != kInvalidCell ? atomicAdd(&cnt[sort_one_word(key[q])], 1u) : 0u;
   }
@@ -274,18 +284,49 @@ __global__ void __launch_bounds__(1024) k_sort_one(const uint32_t* cell, const T
   }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < kSortOnePer; ++q) {
-    if (key[q] == kInvalidCell) continue;
-    const uint32_t i = tid + 1024u * q, to = cnt[sort_one_word(key[q])] + rank[q];
-    cell_o[to] = key[q];
-    ox_o[to] = ox[i];
-    oy_o[to] = oy[i];
-    oz_o[to] = oz[i];
-    w_o[to] = wi[q];
-    id_o[to] = id[i];
+  for (int q = 0; q < kPer; ++q)  // the particle's slot
+    if (key[q] != kInvalidCell) rank[q] += cnt[sort_one_word(key[q])];
+  if constexpr (kStraight) {
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (key[q] == kInvalidCell) continue;
+      const uint32_t i = tid + 1024u * q, to = rank[q];
+      cell_o[to] = key[q];
+      ox_o[to] = ox[i];
+      oy_o[to] = oy[i];
+      oz_o[to] = oz[i];
+      w_o[to] = wi[q];
+      id_o[to] = id[i];
+    }
   }
 #pragma unroll 8
   for (uint32_t c = tid; c < ncell; c += 1024) start[c] = cnt[sort_one_word(c)];
+  if constexpr (!kStraight) {
+    // through the counters' space, once they are read
+    const auto move = [&](auto* out, auto value) {
+      using V = std::remove_pointer_t<decltype(out)>;
+      V* const buf = reinterpret_cast<V*>(cnt);
+      V v[kPer];
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) v[q] = key[q] != kInvalidCell ? value(q) : V{};
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kPer; ++q)
+        if (key[q] != kInvalidCell) buf[rank[q]] = v[q];
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        const uint32_t t = tid + 1024u * q;
+        if (t < total) out[t] = buf[t];
+      }
+    };
+    move(cell_o, [&](int q) { return key[q]; });
+    move(w_o, [&](int q) { return wi[q]; });
+    move(ox_o, [&](int q) { return ox[tid + 1024u * q]; });
+    move(oy_o, [&](int q) { return oy[tid + 1024u * q]; });
+    move(oz_o, [&](int q) { return oz[tid + 1024u * q]; });
+    move(id_o, [&](int q) { return id[tid + 1024u * q]; });
+  }
   if (tid == 0) {
     start[ncell] = total;
     *n_out = total;
@@ -310,15 +351,21 @@ int sort_run(int precision, uint64_t n, uint32_t ncell, const uint32_t* cell, co
   const uint32_t nblk = (ncell + kSortTile - 1) / kSortTile;
   const uint32_t nn = (uint32_t)n;
   if (nn <= kSortOneN && ncell <= kSortOneCells) {
-    const size_t lds = ((size_t)sort_one_word(ncell - 1) / 4 + 1) * 16;
-    if (precision == ITOKMC_FP64)
-      k_sort_one<double><<<1, 1024, lds, s>>>(cell, (const double*)ox, (const double*)oy, (const double*)oz, w, id,
-                                              nn, ncell, cell_o, (double*)ox_o, (double*)oy_o, (double*)oz_o,
-                                              w_o, id_o, start, n_out);
-    else
-      k_sort_one<float><<<1, 1024, lds, s>>>(cell, (const float*)ox, (const float*)oy, (const float*)oz, w, id, nn,
-                                             ncell, cell_o, (float*)ox_o, (float*)oy_o, (float*)oz_o, w_o, id_o,
-                                             start, n_out);
+    const bool straight = nn <= kSortOneStraight;
+    const size_t counters = ((size_t)sort_one_word(ncell - 1) / 4 + 1) * 16;
+    const size_t lds = straight ? counters : std::max(counters, (size_t)nn * 8);
+    const auto go = [&](auto kern, auto t) {
+      using T = decltype(t);
+      kern<<<1, 1024, lds, s>>>(cell, (const T*)ox, (const T*)oy, (const T*)oz, w, id, nn, ncell, cell_o, (T*)ox_o,
+                                (T*)oy_o, (T*)oz_o, w_o, id_o, start, n_out);
+    };
+    if (precision == ITOKMC_FP64) {
+      if (straight) go(k_sort_one<double, true>, 0.0);
+      else go(k_sort_one<double, false>, 0.0);
+    } else {
+      if (straight) go(k_sort_one<float, true>, 0.0f);
+      else go(k_sort_one<float, false>, 0.0f);
+    }
     return hipGetLastError() == hipSuccess ? ITOKMC_OK : ITOKMC_EHIP;
   }
   // the counters start from zero on every call (a fill kernel, so that a captured call
