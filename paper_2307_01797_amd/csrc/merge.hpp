@@ -311,7 +311,10 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
     // (ii) order each splitting leaf by (coordinate, id); copy the other leaves.  Small
     // paths: by the coordinate, and again with the id ranks if (iii) finds that two pieces
     // took one slot.
-    for (bool ties = !contig;; ties = true) {
+    // (A cell with one tie mostly has more: the larger of the small stagings goes by both from
+    // then on.  In the common one that costs a wavefront a SIMD, 2% of every coupling.)
+    constexpr bool kTieForm = contig && CAP > kMergeTiny;
+    for (bool ties = !contig || (kTieForm && ranked);; ties = true) {
     if (contig && ties && !ranked) {
       // id ranks among the cell's pieces (a split superparticle's parts share theirs: they
       // are never in one leaf), with the ids in registers
@@ -364,8 +367,17 @@ __device__ int merge_cell(Bank b, Counters* ctr, int which, const StepConst& K, 
           for (; r < rend; ++r) rank += kkey[r] < kq ? 1u : 0u;
         } else {
           const uint32_t iq = src[pq];
+          uint32_t r = Ls;
+          if constexpr (kTieForm) {  // the loads of four pieces in flight together
+            for (; r + 4 <= rend; r += 4) {
+              const T k4[4] = {kkey[r], kkey[r + 1], kkey[r + 2], kkey[r + 3]};
+              const uint32_t i4[4] = {src[I(cb)[r]], src[I(cb)[r + 1]], src[I(cb)[r + 2]], src[I(cb)[r + 3]]};
+#pragma unroll
+              for (int a = 0; a < 4; ++a) rank += (k4[a] < kq) | ((k4[a] == kq) & (i4[a] < iq)) ? 1u : 0u;
+            }
+          }
 #pragma unroll 1
-          for (uint32_t r = Ls; r < rend; ++r) {
+          for (; r < rend; ++r) {
             const T kr = kkey[r];
             rank += (kr < kq || (kr == kq && src[I(cb)[r]] < iq)) ? 1u : 0u;
           }
