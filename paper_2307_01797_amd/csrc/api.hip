@@ -651,9 +651,10 @@ int itokmc_set_particles(itokmc_ctx* ctx, uint64_t n, const uint32_t* cell, cons
     for (int a = 0; a < 3; ++a) {
       ho[a].resize((size_t)n * (f64 ? 8 : 4));
       for (uint64_t i = 0; i < n; ++i) {
-        if (f64) ((double*)ho[a].data())[i] = off[3 * i + a];
+        const double o = off[3 * i + a] + 0.0;  // a negative zero becomes a zero
+        if (f64) ((double*)ho[a].data())[i] = o;
         else {
-          float f = (float)off[3 * i + a];
+          float f = (float)o;
           ((float*)ho[a].data())[i] = f < 1.0f ? f : 0x1.fffffep-1f;
         }
       }

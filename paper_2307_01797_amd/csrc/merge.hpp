@@ -38,18 +38,19 @@ template <typename T> struct MergeBig;
 template <> struct MergeBig<float> { static constexpr int value = 1536; };
 template <> struct MergeBig<double> { static constexpr int value = 1024; };
 
-// Bit pattern whose unsigned order is the order of non-negative values (x + 0: a negative
-// zero, which compares equal to zero, must not become the largest pattern).
+// Bit pattern whose unsigned order is the order of non-negative values (no offset in a bank
+// is a negative zero, which would be the largest pattern: itokmc_set_particles takes the sign
+// off and the kernels make none).
 template <typename T> struct Bits;
 template <> struct Bits<float> {
   using U = uint32_t;
-  __device__ static U of(float x) { return __float_as_uint(x + 0.0f); }
+  __device__ static U of(float x) { return __float_as_uint(x); }
   __device__ static float val(U u) { return __uint_as_float(u); }
   static constexpr U lo_init = 0xFFFFFFFFu;
 };
 template <> struct Bits<double> {
   using U = unsigned long long;
-  __device__ static U of(double x) { return (U)__double_as_longlong(x + 0.0); }
+  __device__ static U of(double x) { return (U)__double_as_longlong(x); }
   __device__ static double val(U u) { return __longlong_as_double((long long)u); }
   static constexpr U lo_init = ~0ull;
 };
