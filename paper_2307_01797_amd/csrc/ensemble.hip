@@ -356,12 +356,15 @@ __global__ void __launch_bounds__(1024, sizeof(T) == 4 ? 8 : 4) e_push(Bank a, C
 constexpr int kEnsKmcPer = 4;
 constexpr int kTallies = 5;  // fires x3, created, removed weight
 
-struct KmcLds {  // workgroups of up to 256 threads
+constexpr int kKmcThreads = 256;  // the largest workgroup
+constexpr int kKmcWaves = kKmcThreads / 64;
+
+struct KmcLds {
   unsigned long long tally[kTallies];
-  uint32_t prod[4];        // the wavefronts' products of the span's realization
+  uint32_t prod[kKmcWaves];      // the wavefronts' products of the span's realization
   uint32_t prod_base;      // products of the realization reserved before this span
   uint32_t capped;         // the span's products exceed its quota
-  uint32_t tot[3][4];      // the wavefronts' deferred cells, queued cells and products
+  uint32_t tot[3][kKmcWaves];    // the wavefronts' deferred cells, queued cells and products
   uint32_t base[3];        // and the workgroup's first slots
 };
 
@@ -551,7 +554,7 @@ __device__ __forceinline__ void kmc_phase(
 }
 
 template <bool kFast>
-__global__ void __launch_bounds__(kFast ? 256 : 64) e_kmc(
+__global__ void __launch_bounds__(kFast ? kKmcThreads : 64) e_kmc(
     Counters* ctr, const uint32_t* occ, unsigned long long* cellacc, uint32_t* nplus,
     uint32_t* nminus, int32_t* dN, uint32_t* work, uint32_t* cbase, uint32_t* heavy,
     const SlotConst* sc, const int32_t* blk_slot, const uint32_t* blk_local,
@@ -895,6 +898,9 @@ struct FuseArgs {
 template <typename T, int W>
 __global__ void __launch_bounds__(kFuseBlock, W) e_step_fused(FuseArgs A) {
   __shared__ __align__(16) uint32_t sh[kScanCells + 2 * (kFuseBlock / 64) + 2];
+  // the phases take turns with it
+  static_assert(sizeof(PushLds) <= sizeof(sh) && sizeof(KmcLds) <= sizeof(sh), "LDS of the push and KMC phases");
+  static_assert(kFuseBlock <= kKmcThreads, "KMC phase: one slot per wavefront");
   __shared__ uint32_t flag;
   const uint32_t bid = blockIdx.x, G = gridDim.x;
   const uint32_t tid = bid * blockDim.x + threadIdx.x, nthr = G * blockDim.x;
@@ -1797,7 +1803,7 @@ int itokmc_ensemble_set_tuning(itokmc_ens* e, const itokmc_ens_tuning* t) {
   if (!e || !t) return ITOKMC_EINVAL;
   if (t->push_block < 64 || t->push_block > 1024 || t->push_block % 64 ||
       t->push_blocks_per_cu < 1 || t->push_blocks_per_cu > 64 ||
-      (t->kmc_block != 64 && t->kmc_block != 128 && t->kmc_block != 256) ||
+      (t->kmc_block != kKmcThreads / 4 && t->kmc_block != kKmcThreads / 2 && t->kmc_block != kKmcThreads) ||
       t->couple_per_cu < 1 || t->couple_per_cu > 256 ||
       (t->fused_per_cu != 0 && t->fused_per_cu != 1 && t->fused_per_cu != 2 && t->fused_per_cu != 4))
     return ens_error(e, ITOKMC_EINVAL, "tuning out of range");
